@@ -79,6 +79,31 @@ __global__ void current_units(StoreDesc* __restrict__ stores, int nstores) {
   D.g.jinv = ldexpf(1.0f, -e);
 }
 
+// Which field step a periodic 3D box takes: runs of planes along z
+// (yee_march3) or 16x4x4 tiles (yee_step).
+// A long run re-reads little (two planes of E and one of B at its start), but
+// its planes are a serial chain of three barriers and one memory latency
+// each, so the run shortens until the box makes 1,024 workgroups (four per
+// CU), down to 8 planes; a box that does not make 512 workgroups of 8-plane
+// runs takes yee_step's 16x4x4 tiles, which have no chain.  Measured with
+// tiles and with runs of 8, 16 and 32 planes: 128x64x64 25, 29, 42, 69 us;
+// 160x96x96 54, 47, 52, 70 us; 256x128x128 197, 124, 119, 127 us;
+// 512x256x256 1456, 819, 753, 728 us.
+struct MarchTile { static constexpr int X = 32, Y = 8; };
+constexpr int kMarchMin = 8, kMarchMax = 32;
+
+__host__ __device__ inline int march_columns(const int nx[3]) {
+  return ((nx[0] + MarchTile::X - 1) / MarchTile::X) * ((nx[1] + MarchTile::Y - 1) / MarchTile::Y);
+}
+
+// planes per run of a box, 0 for a box that takes the tiles
+__host__ __device__ inline int march_run(const int nx[3]) {
+  const int cols = march_columns(nx);
+  int r = kMarchMax;
+  while (r > kMarchMin && cols * ((nx[2] + r - 1) / r) < 1024) r /= 2;
+  return cols * ((nx[2] + r - 1) / r) < 512 ? 0 : r;
+}
+
 template <int DIM, bool WIN>
 __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ inst, int par) {
   using T = YeeTile<DIM>;
@@ -89,6 +114,7 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
   const InstDesc& I = inst[blockIdx.y];
   const GridDesc& g = I.g;
   if (g.cyl) return;  // r-z instances take yee_step_rz
+  if (DIM == 3 && !WIN && march_run(g.nx) > 0) return;  // takes yee_march3
   const int ntx = (g.nx[0] + T::X - 1) / T::X;
   const int nty = (g.nx[1] + T::Y - 1) / T::Y;
   const int ntz = DIM == 3 ? (g.nx[2] + T::Z - 1) / T::Z : 1;
@@ -301,7 +327,7 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
 }
 
 // The periodic 3D field step marching along z.  A workgroup owns a 32x8
-// column of cells in x-y and a run of kMarchZ planes, and keeps a rolling
+// column of cells in x-y and a run of planes (march_run), and keeps a rolling
 // window of planes in LDS: E at z+1 and z+2, Bh at z and z+1, E' at z and
 // z+1.  Each plane of E, B and J is read once per column (plus the x-y halo
 // and two planes at the start of a run), instead of once per 16x4x4 tile
@@ -313,8 +339,6 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
 // x-y indices are region-relative with the origin one node below the column
 // (E region 35x11, B region 34x10); E' is formed on nodes 1..e+1, B' on the
 // column's own nodes 1..e.
-struct MarchTile { static constexpr int X = 32, Y = 8; };
-constexpr int kMarchZ = 32;
 constexpr int kMarchE = (MarchTile::X + 3) * (MarchTile::Y + 3);
 constexpr int kMarchB = (MarchTile::X + 2) * (MarchTile::Y + 2);
 
@@ -328,14 +352,16 @@ __global__ void __launch_bounds__(kBlock) yee_march3(const InstDesc* __restrict_
   const int n0 = g.nx[0], n1 = g.nx[1], n2 = g.nx[2];
   const int ntx = (n0 + MarchTile::X - 1) / MarchTile::X;
   const int nty = (n1 + MarchTile::Y - 1) / MarchTile::Y;
-  const int ntz = (n2 + kMarchZ - 1) / kMarchZ;
+  const int run = march_run(g.nx);
+  if (run == 0) return;  // takes yee_step's tiles
+  const int ntz = (n2 + run - 1) / run;
   const int tile = blockIdx.x;
   if (tile >= ntx * nty * ntz) return;
   const int tid = threadIdx.x;
   const int o0 = (tile % ntx) * MarchTile::X;
   const int o1 = ((tile / ntx) % nty) * MarchTile::Y;
-  const int z0 = (tile / (ntx * nty)) * kMarchZ;
-  const int z1 = min(z0 + kMarchZ, n2);
+  const int z0 = (tile / (ntx * nty)) * run;
+  const int z1 = min(z0 + run, n2);
   const int e0 = min(MarchTile::X, n0 - o0), e1 = min(MarchTile::Y, n1 - o1);
   const int EX = e0 + 3, EY = e1 + 3, BX = e0 + 2, BY = e1 + 2;
   const int EN = EX * EY, BN = BX * BY, PX = e0 + 1, PN = PX * (e1 + 1);
@@ -622,28 +648,56 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
     int r = wrap1(o0 - 1 + x, n0) - wo;
     return r < 0 ? r + n0 : r;
   };
-  // region node (x, y) is column o0 - 1 + x (periodic) and row o1 - 1 + y
+  // region node (x, y) is column o0 - 1 + x (periodic) and row o1 - 1 + y.
+  // Staged in flat order, two nodes per thread with every load in flight
+  // before the first LDS write, so a workgroup waits here for one memory
+  // latency instead of up to four: 4.3 us a step less on a box of 384x96 (144
+  // workgroups; the kernel took 15.3 us before).
   const gfloat* F = (const gfloat*)I.F[par];
-  for (int y = ty; y < EY; y += T::Y)
-    for (int x = tx; x < EX; x += T::X) {
-      const int gx = wrap1(o0 - 1 + x, n0);
-      const int ry = o1 - 1 + y;
-      const int rw = ry <= 0 ? 1 - ry : ry;
-      const int rh = ry < 0 ? -ry : ry;
-      const float sw = ry <= 0 ? -1.0f : 1.0f, sh = ry < 0 ? -1.0f : 1.0f;
-      const bool iw = rw < n1, ih = rh < n1;
-      const int gw = gx + n0 * rw, gh = gx + n0 * rh;
-      const int r = x + EX * y;
-      sE[0][r] = iw ? F[gw] : 0.0f;
-      sE[1][r] = ih ? sh * F[nc + gh] : 0.0f;
-      sE[2][r] = iw ? sw * F[2 * nc + gw] : 0.0f;
-      if (x < BX && y < BY) {
-        const int rb = x + BX * y;
-        sB[0][rb] = ih ? F[3 * nc + gh] : 0.0f;
-        sB[1][rb] = iw ? sw * F[4 * nc + gw] : 0.0f;
-        sB[2][rb] = ih ? sh * F[5 * nc + gh] : 0.0f;
+  {
+    constexpr int U = 2;  // EXM * EYM <= U * kBlock
+    static_assert(EXM * EYM <= U * kBlock, "one round stages the region");
+    const int EN = EX * EY;
+    float v[U][6];
+    int rb[U];
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      const int q = threadIdx.x + k * kBlock;
+      rb[k] = -1;
+      if (q < EN) {
+        const int x = q % EX, y = q / EX;
+        const int gx = wrap1(o0 - 1 + x, n0);
+        const int ry = o1 - 1 + y;
+        const int rw = ry <= 0 ? 1 - ry : ry;
+        const int rh = ry < 0 ? -ry : ry;
+        const float sw = ry <= 0 ? -1.0f : 1.0f, sh = ry < 0 ? -1.0f : 1.0f;
+        const bool iw = rw < n1, ih = rh < n1;
+        const int gw = gx + n0 * rw, gh = gx + n0 * rh;
+        v[k][0] = iw ? F[gw] : 0.0f;
+        v[k][1] = ih ? sh * F[nc + gh] : 0.0f;
+        v[k][2] = iw ? sw * F[2 * nc + gw] : 0.0f;
+        if (x < BX && y < BY) {
+          rb[k] = x + BX * y;
+          v[k][3] = ih ? F[3 * nc + gh] : 0.0f;
+          v[k][4] = iw ? sw * F[4 * nc + gw] : 0.0f;
+          v[k][5] = ih ? sh * F[5 * nc + gh] : 0.0f;
+        }
       }
     }
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      const int q = threadIdx.x + k * kBlock;
+      if (q >= EN) continue;
+      sE[0][q] = v[k][0];
+      sE[1][q] = v[k][1];
+      sE[2][q] = v[k][2];
+      if (rb[k] >= 0) {
+        sB[0][rb[k]] = v[k][3];
+        sB[1][rb[k]] = v[k][4];
+        sB[2][rb[k]] = v[k][5];
+      }
+    }
+  }
   __syncthreads();
   const float h = 0.5f * g.dt;
   const float rz = g.rdx[0], rr = g.rdx[1];
@@ -912,16 +966,18 @@ hipError_t pic_launch_smooth_pass(const InstDesc* d_inst, int ninst, int max_nce
   return hipGetLastError();
 }
 
-int pic_yee_tiles(int dim, const int nx[3]) {
+int pic_yee_tiles(int dim, const int nx[3], bool window) {
   if (dim == 2)
     return ((nx[0] + YeeTile<2>::X - 1) / YeeTile<2>::X) * ((nx[1] + YeeTile<2>::Y - 1) / YeeTile<2>::Y);
-  // the larger of the tile counts of yee_step (moving windows) and yee_march3
-  const int t = ((nx[0] + YeeTile<3>::X - 1) / YeeTile<3>::X) * ((nx[1] + YeeTile<3>::Y - 1) / YeeTile<3>::Y) *
-                ((nx[2] + YeeTile<3>::Z - 1) / YeeTile<3>::Z);
-  const int m = ((nx[0] + MarchTile::X - 1) / MarchTile::X) * ((nx[1] + MarchTile::Y - 1) / MarchTile::Y) *
-                ((nx[2] + kMarchZ - 1) / kMarchZ);
-  return t > m ? t : m;
+  if (!window && march_run(nx) > 0) {
+    const int r = march_run(nx);
+    return march_columns(nx) * ((nx[2] + r - 1) / r);
+  }
+  return ((nx[0] + YeeTile<3>::X - 1) / YeeTile<3>::X) * ((nx[1] + YeeTile<3>::Y - 1) / YeeTile<3>::Y) *
+         ((nx[2] + YeeTile<3>::Z - 1) / YeeTile<3>::Z);
 }
+
+bool pic_yee_marches(const int nx[3]) { return march_run(nx) > 0; }
 
 hipError_t pic_launch_current_units(StoreDesc* d_stores, int nstores, hipStream_t st) {
   hipLaunchKernelGGL(current_units, dim3((nstores + 63) / 64), dim3(64), 0, st, d_stores, nstores);
@@ -929,7 +985,7 @@ hipError_t pic_launch_current_units(StoreDesc* d_stores, int nstores, hipStream_
 }
 
 hipError_t pic_launch_yee_step(const InstDesc* d_inst, int ninst, int max_tiles, int dim, bool cart, bool cyl,
-                               bool window, int parity, hipStream_t st) {
+                               bool window, bool march, bool tiles, int parity, hipStream_t st) {
   const dim3 grid(max_tiles, ninst);
   if (dim == 2) {
     if (cart && window) hipLaunchKernelGGL((yee_step<2, true>), grid, dim3(kBlock), 0, st, d_inst, parity);
@@ -938,7 +994,8 @@ hipError_t pic_launch_yee_step(const InstDesc* d_inst, int ninst, int max_tiles,
   } else if (window) {
     hipLaunchKernelGGL((yee_step<3, true>), grid, dim3(kBlock), 0, st, d_inst, parity);
   } else {
-    hipLaunchKernelGGL(yee_march3, grid, dim3(kBlock), 0, st, d_inst, parity);
+    if (march) hipLaunchKernelGGL(yee_march3, grid, dim3(kBlock), 0, st, d_inst, parity);
+    if (tiles) hipLaunchKernelGGL((yee_step<3, false>), grid, dim3(kBlock), 0, st, d_inst, parity);
   }
   return hipGetLastError();
 }

@@ -34,18 +34,21 @@ hipError_t pic_launch_gpd(int dim, int order, int mode, const StoreDesc* d_store
                           size_t lds, int parity, int kstep, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 
 // Yee field solve (field.hip); instances in d_inst[0..ninst)
-int pic_yee_tiles(int dim, const int nx[3]);
+int pic_yee_tiles(int dim, const int nx[3], bool window);
+// whether a periodic 3D box takes the field step that marches along z
+bool pic_yee_marches(const int nx[3]);
 hipError_t pic_launch_window_advance(const InstDesc* d_inst, int ninst, hipStream_t st);
 hipError_t pic_launch_smooth_pass(const InstDesc* d_inst, int ninst, int max_ncell, int axis, int lev,
                                   int parity, hipStream_t st);
 // cart / cyl: the group holds Cartesian / r-z instances (each kernel skips the
 // others); window: some instance has a moving window (selects the variant
-// with the window terms)
+// with the window terms); march / tiles: without a window, the group holds 3D
+// boxes that march along z / that take the 3D tiles
 // Per store: this step's fixed point of the one-phase kernels' FP32 current
 // (from the store's bound on |u| and the instance's bound on |E_c|).
 hipError_t pic_launch_current_units(StoreDesc* d_stores, int nstores, hipStream_t st);
 hipError_t pic_launch_yee_step(const InstDesc* d_inst, int ninst, int max_tiles, int dim, bool cart, bool cyl,
-                               bool window, int parity, hipStream_t st);
+                               bool window, bool march, bool tiles, int parity, hipStream_t st);
 
 // tile rebin (sort.hip); stores in d_stores[0..nstores)
 hipError_t pic_launch_rebin(const StoreDesc* d_stores, int nstores, int max_items, int total_tiles,

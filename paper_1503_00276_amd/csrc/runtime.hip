@@ -78,6 +78,7 @@ struct Group {
   std::vector<size_t> lds_k;
   std::vector<int> res_k;
   bool cyl = false, cart = false;  // instances: some are r-z / some are Cartesian
+  bool march = false, tiles3 = false;  // periodic 3D instances: some march along z / some take tiles
 };
 
 // Boundary logic an instance's stores need in the fused particle kernel.
@@ -543,8 +544,11 @@ pic_status refresh_descriptors(Sim& S) {
       if (I.g.acc_mode == PIC_ACC_FIXED64) gr.fixed64 = true;
       gr.count++;
       gr.max_ncell = std::max(gr.max_ncell, I.g.ncell);
-      gr.max_tiles = std::max(gr.max_tiles, pic_yee_tiles(dim, I.g.nx));
+      if (dim == 3) (pic_yee_marches(I.g.nx) ? gr.march : gr.tiles3) = true;
     }
+    // (a group with a moving window takes the tiles for every instance)
+    for (size_t i = 0; i < S.inst.size(); i++)
+      if (S.inst[i].g.dim == dim) gr.max_tiles = std::max(gr.max_tiles, pic_yee_tiles(dim, S.inst[i].g.nx, gr.window));
     if (gr.count > 0) S.igroups.push_back(gr);
   }
   if ((int)stores.size() > S.d_stores_cap) {
@@ -668,7 +672,7 @@ pic_status launch_steps(Sim& S, int64_t first, int nsteps, bool end_with_check, 
           HIPCHK(S, pic_launch_smooth_pass(S.d_inst + gr.first, gr.count, gr.max_ncell, a, lev, par, S.stream));
     for (const Group& gr : S.igroups)
       HIPCHK(S, pic_launch_yee_step(S.d_inst + gr.first, gr.count, gr.max_tiles, gr.dim, gr.cart, gr.cyl,
-                                    gr.window, par, S.stream));
+                                    gr.window, gr.march, gr.tiles3, par, S.stream));
     prof_end(S, 1, e0);
     if (end_with_check && k == nsteps - 1) {
       e0 = prof_begin(S);
