@@ -55,7 +55,9 @@ hipError_t pic_launch_rebin(const StoreDesc* d_stores, int nstores, int max_item
                             int total_blocks, int inject_max, hipStream_t st);
 
 // diagnostics (diag.hip)
-hipError_t pic_launch_rho64(const StoreDesc* d_store, int np_max, double* rho, hipStream_t st);
+// adds a species' charge density; kstep: steps done since the last rebin check
+hipError_t pic_launch_rho64(const StoreDesc* d_store, const GridDesc& g, int max_items, int kstep, double* rho,
+                            hipStream_t st);
 hipError_t pic_launch_fill64(double* p, double v, size_t n, hipStream_t st);
 // r-z: rho = ion + folded charge / (r_j/dr) on rows j >= 1, row 0 = row 1
 hipError_t pic_launch_rz_rho_finish(double* rho, int nz, int nr, double ion, hipStream_t st);

@@ -1182,7 +1182,8 @@ pic_status compute_rho(Sim& S, int i, double* d_rho) {
     if (!I.sp[s].used || I.sp[s].np == 0) continue;
     int k = store_desc_index(S, i, s);
     if (k < 0) return S.fail(PIC_E_STATE, "species descriptor missing");
-    HIPCHK(S, pic_launch_rho64(S.d_stores + k, (int)I.sp[s].np, d_rho, S.stream));
+    HIPCHK(S, pic_launch_rho64(S.d_stores + k, I.g, I.sp[s].max_items, (int)(S.steps % S.sort_interval), d_rho,
+                               S.stream));
   }
   if (I.g.cyl) HIPCHK(S, pic_launch_rz_rho_finish(d_rho, I.g.nx[0], I.g.nx[1], I.cfg.ion_density, S.stream));
   return PIC_OK;
