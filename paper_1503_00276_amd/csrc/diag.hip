@@ -55,7 +55,7 @@ constexpr int kRhoPer = 4;  // particles per thread and pass over a tile
 // nodes in LDS and the sums are added to the global array once.  Adding every
 // particle's (ORDER+1)^DIM contributions to the global array with FP64 atomics
 // cost 26.5 ms for 16.8 M particles of a cubic shape (64 each, 40 G adds/s);
-// this kernel adds about three sums per particle there and takes 0.45 ms.
+// this kernel adds about three sums per particle there and takes 0.72 ms.
 //
 // The LDS sums are integers (LDS integer adds run several times faster than
 // floating ones, and their sum does not depend on the order): a pass takes at
@@ -65,7 +65,7 @@ constexpr int kRhoPer = 4;  // particles per thread and pass over a tile
 // sum.  The rounding is 2^-52 of the pass's largest weight, that of an FP64
 // add to a node holding one such particle, and 1024 of them stay below 2^62.
 template <int DIM, int ORDER>
-__global__ void __launch_bounds__(kBlock) rho64(const StoreDesc* __restrict__ sp, double* rho, int kstep) {
+__global__ void __launch_bounds__(kBlock) rho64(const StoreDesc* __restrict__ sp, double* rho, int kstep, int par) {
   extern __shared__ unsigned long long sR[];
   __shared__ float s_w[kBlock / 64];
   constexpr int NO = ORDER + 1;
@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(kBlock) rho64(const StoreDesc* __restrict__ sp
   const int total = S.ctl->n_items[cur];
   const int s0 = S.ctl->sorted ? 0 : g.flag_slack;
   const int tid = threadIdx.x;
-  const int wo = g.window ? S.win->origin : 0;
+  const int wo = g.window ? S.win[par].origin : 0;
   const int lo = rho_below(ORDER), hi = rho_above(ORDER);
   for (int ii = blockIdx.x; ii < total; ii += gridDim.x) {
     const Item it = S.items[cur][ii];
@@ -237,15 +237,15 @@ __global__ void __launch_bounds__(kBlock) gauss64(const InstDesc* __restrict__ i
   const InstDesc& I = *ip;
   const int nc = I.g.ncell;
   for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += gridDim.x * blockDim.x)
-    G[c] = div_at(I.g, I.F[fpar], nc, c, dim, I.g.window ? I.win->origin : -1) - rho[c];
+    G[c] = div_at(I.g, I.F[fpar], nc, c, dim, I.g.window ? I.win[fpar].origin : -1) - rho[c];
 }
 
 __global__ void __launch_bounds__(kBlock) charge64(const InstDesc* __restrict__ ip, const double* rho0,
-                                                   const double* rho1, double* C, int dim) {
+                                                   const double* rho1, double* C, int dim, int par) {
   const InstDesc& I = *ip;
   const int nc = I.g.ncell;
   for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += gridDim.x * blockDim.x)
-    C[c] = (rho1[c] - rho0[c]) / I.g.dtd + div_at(I.g, I.Jout, nc, c, dim, I.g.window ? I.win->origin : -1);
+    C[c] = (rho1[c] - rho0[c]) / I.g.dtd + div_at(I.g, I.Jout, nc, c, dim, I.g.window ? I.win[par].origin : -1);
 }
 
 // ---------------------------------------------------------------------------
@@ -428,7 +428,7 @@ int grid_for(size_t n) {
 
 int pic_reduce_blocks() { return kRedBlocks; }
 
-hipError_t pic_launch_rho64(const StoreDesc* d_store, const GridDesc& g, int max_items, int kstep, double* rho,
+hipError_t pic_launch_rho64(const StoreDesc* d_store, const GridDesc& g, int max_items, int kstep, int par, double* rho,
                             hipStream_t st) {
   // the largest region: flag_slack is the base after a check that did not re-sort
   size_t lds = sizeof(unsigned long long);
@@ -436,13 +436,13 @@ hipError_t pic_launch_rho64(const StoreDesc* d_store, const GridDesc& g, int max
     lds *= (size_t)(g.tile[d] + 2 * rho_stray(g, d, g.flag_slack, kstep) + rho_below(g.order) + rho_above(g.order));
   const dim3 grid(max_items < 1 ? 1 : (max_items > 4096 ? 4096 : max_items));
   if (g.dim == 2) {
-    if (g.order == 1) rho64<2, 1><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep);
-    if (g.order == 2) rho64<2, 2><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep);
-    if (g.order == 3) rho64<2, 3><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep);
+    if (g.order == 1) rho64<2, 1><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep, par);
+    if (g.order == 2) rho64<2, 2><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep, par);
+    if (g.order == 3) rho64<2, 3><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep, par);
   } else {
-    if (g.order == 1) rho64<3, 1><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep);
-    if (g.order == 2) rho64<3, 2><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep);
-    if (g.order == 3) rho64<3, 3><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep);
+    if (g.order == 1) rho64<3, 1><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep, par);
+    if (g.order == 2) rho64<3, 2><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep, par);
+    if (g.order == 3) rho64<3, 3><<<grid, dim3(kBlock), lds, st>>>(d_store, rho, kstep, par);
   }
   return hipGetLastError();
 }
@@ -465,8 +465,8 @@ hipError_t pic_launch_gauss64(const InstDesc* d_inst, const double* rho, double*
 }
 
 hipError_t pic_launch_charge64(const InstDesc* d_inst, const double* rho0, const double* rho1, double* C,
-                               int ncell, int dim, hipStream_t st) {
-  hipLaunchKernelGGL(charge64, dim3(grid_for(ncell)), dim3(kBlock), 0, st, d_inst, rho0, rho1, C, dim);
+                               int ncell, int dim, int par, hipStream_t st) {
+  hipLaunchKernelGGL(charge64, dim3(grid_for(ncell)), dim3(kBlock), 0, st, d_inst, rho0, rho1, C, dim, par);
   return hipGetLastError();
 }
 

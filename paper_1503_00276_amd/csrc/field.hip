@@ -10,6 +10,7 @@
 // neighbours by wrap; blockIdx.y selects the instance of a batch.
 #include "pic_dev.h"
 #include "pic_kernels.h"
+#include "pic_plan.h"
 
 namespace {
 
@@ -104,8 +105,35 @@ __host__ __device__ inline int march_run(const int nx[3]) {
   return cols * ((nx[2] + r - 1) / r) < 512 ? 0 : r;
 }
 
+// The first blocks of a field step's launch (x below npx, over all y) plan the
+// rebin check of one store each, beside the field update, which neither reads
+// nor writes anything of it: returns true for them.
+__device__ __forceinline__ bool plan_block(const StoreDesc* __restrict__ plan, int nplan, int npx, int par) {
+  if ((int)blockIdx.x >= npx) return false;
+  const int s = blockIdx.x * gridDim.y + blockIdx.y;
+  if (s < nplan && plan[s].g.ntiles <= PIC_PLAN_TILES) plan_store<kBlock>(plan[s], par);
+  return true;
+}
+
+// End of a step of a moving window, by one thread per instance: count the step
+// and, when c t has passed the next whole cell, move the window (advance the
+// ring origin, count the injected particles' ids), in the other parity's entry.
+__device__ __forceinline__ void window_advance(const InstDesc& I, int par) {
+  WinCtl w = I.win[par];
+  const bool sh = pic_win_shifts(I.g.wa, w.step + 1) > pic_win_shifts(I.g.wa, w.step);
+  w.step += 1;
+  if (sh) {
+    w.shifts += 1;
+    w.origin = w.origin + 1 == I.g.nx[0] ? 0 : w.origin + 1;
+    w.next_id += I.win_inject;
+  }
+  I.win[1 - par] = w;
+}
+
 template <int DIM, bool WIN>
-__global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ inst, int par) {
+__global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ inst, int par,
+                                                   const StoreDesc* __restrict__ plan, int nplan, int npx) {
+  if (plan_block(plan, nplan, npx, par)) return;
   using T = YeeTile<DIM>;
   constexpr int EXM = T::X + 3, EYM = T::Y + 3, EZM = DIM == 3 ? T::Z + 3 : 1;
   constexpr int BXM = T::X + 2, BYM = T::Y + 2, BZM = DIM == 3 ? T::Z + 2 : 1;
@@ -118,7 +146,7 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
   const int ntx = (g.nx[0] + T::X - 1) / T::X;
   const int nty = (g.nx[1] + T::Y - 1) / T::Y;
   const int ntz = DIM == 3 ? (g.nx[2] + T::Z - 1) / T::Z : 1;
-  const int tile = blockIdx.x;
+  const int tile = (int)blockIdx.x - npx;
   // thread layout = tile shape (T::X * T::Y * T::Z == blockDim.x)
   const int tx = threadIdx.x % T::X;
   const int ty = (threadIdx.x / T::X) % T::Y;
@@ -142,9 +170,10 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
     int wo = 0;
     bool wshift = false;
     if (win) {
-      const WinCtl wc = *I.win;
+      const WinCtl wc = I.win[par];
       wo = wc.origin;
       wshift = pic_win_shifts(g.wa, wc.step + 1) > pic_win_shifts(g.wa, wc.step);
+      if (tile == 0 && threadIdx.x == 0) window_advance(I, par);
     }
     auto wcol = [&](int x) {
       int r = wrap1(o0 - 1 + x, n0) - wo;
@@ -342,7 +371,9 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
 constexpr int kMarchE = (MarchTile::X + 3) * (MarchTile::Y + 3);
 constexpr int kMarchB = (MarchTile::X + 2) * (MarchTile::Y + 2);
 
-__global__ void __launch_bounds__(kBlock) yee_march3(const InstDesc* __restrict__ inst, int par) {
+__global__ void __launch_bounds__(kBlock) yee_march3(const InstDesc* __restrict__ inst, int par,
+                                                   const StoreDesc* __restrict__ plan, int nplan, int npx) {
+  if (plan_block(plan, nplan, npx, par)) return;
   __shared__ float sE[2][3][kMarchE];
   __shared__ float sBh[2][3][kMarchB];
   __shared__ float sEp[2][3][kMarchE];
@@ -355,7 +386,7 @@ __global__ void __launch_bounds__(kBlock) yee_march3(const InstDesc* __restrict_
   const int run = march_run(g.nx);
   if (run == 0) return;  // takes yee_step's tiles
   const int ntz = (n2 + run - 1) / run;
-  const int tile = blockIdx.x;
+  const int tile = (int)blockIdx.x - npx;
   if (tile >= ntx * nty * ntz) return;
   const int tid = threadIdx.x;
   const int o0 = (tile % ntx) * MarchTile::X;
@@ -610,7 +641,9 @@ __global__ void __launch_bounds__(kBlock) yee_march3(const InstDesc* __restrict_
 // accumulators hold the folded ring currents: each row is divided by its
 // ring volume (in units of 2 pi dr^2 dz) as it is read, and Jout keeps the
 // current density.
-__global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict__ inst, int par) {
+__global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict__ inst, int par,
+                                                   const StoreDesc* __restrict__ plan, int nplan, int npx) {
+  if (plan_block(plan, nplan, npx, par)) return;
   using T = YeeTile<2>;
   constexpr int EXM = T::X + 3, EYM = T::Y + 3;
   constexpr int BXM = T::X + 2, BYM = T::Y + 2;
@@ -621,7 +654,7 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
   if (!g.cyl) return;
   const int ntx = (g.nx[0] + T::X - 1) / T::X;
   const int nty = (g.nx[1] + T::Y - 1) / T::Y;
-  const int tile = blockIdx.x;
+  const int tile = (int)blockIdx.x - npx;
   if (tile >= ntx * nty) return;
   const int tx = threadIdx.x % T::X;
   const int ty = threadIdx.x / T::X;
@@ -640,9 +673,10 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
   int wo = 0;
   bool wshift = false;
   if (win) {
-    const WinCtl wc = *I.win;
+    const WinCtl wc = I.win[par];
     wo = wc.origin;
     wshift = pic_win_shifts(g.wa, wc.step + 1) > pic_win_shifts(g.wa, wc.step);
+    if (tile == 0 && threadIdx.x == 0) window_advance(I, par);
   }
   auto wcol = [&](int x) {
     int r = wrap1(o0 - 1 + x, n0) - wo;
@@ -854,7 +888,7 @@ __device__ __forceinline__ void smooth_pass_rz(const InstDesc& I, int axis, floa
       // along z: periodic, or zero beyond the ends of a moving window
       float am = a, cp = c;
       if (g.window) {
-        int wr = i - I.win->origin;
+        int wr = i - I.win[par].origin;
         if (wr < 0) wr += n0;
         if (wr == 0) am = 0.0f;
         if (wr == n0 - 1) cp = 0.0f;
@@ -906,7 +940,7 @@ __global__ void __launch_bounds__(kBlock) smooth_pass(const InstDesc* __restrict
     // moving window: beyond the x1 ends the current is zero
     float am = a, cp = c;
     if (g.window && axis == 0) {
-      int wr = i - I.win->origin;
+      int wr = i - I.win[par].origin;
       if (wr < 0) wr += n;
       if (wr == 0) am = 0.0f;
       if (wr == n - 1) cp = 0.0f;
@@ -931,31 +965,7 @@ __global__ void __launch_bounds__(kBlock) smooth_pass(const InstDesc* __restrict
   }
 }
 
-// End of a step of a moving window: count the step and, when c t has passed
-// the next whole cell, move the window (advance the ring origin, count the
-// injected particles' ids).  One thread per instance.
-__global__ void window_advance(const InstDesc* __restrict__ inst, int ninst) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= ninst) return;
-  const InstDesc& I = inst[k];
-  if (!I.g.window) return;
-  WinCtl w = *I.win;
-  const bool sh = pic_win_shifts(I.g.wa, w.step + 1) > pic_win_shifts(I.g.wa, w.step);
-  w.step += 1;
-  if (sh) {
-    w.shifts += 1;
-    w.origin = w.origin + 1 == I.g.nx[0] ? 0 : w.origin + 1;
-    w.next_id += I.win_inject;
-  }
-  *I.win = w;
-}
-
 }  // namespace
-
-hipError_t pic_launch_window_advance(const InstDesc* d_inst, int ninst, hipStream_t st) {
-  hipLaunchKernelGGL(window_advance, dim3((ninst + 63) / 64), dim3(64), 0, st, d_inst, ninst);
-  return hipGetLastError();
-}
 
 hipError_t pic_launch_smooth_pass(const InstDesc* d_inst, int ninst, int max_ncell, int axis, int lev,
                                   int parity, hipStream_t st) {
@@ -985,17 +995,23 @@ hipError_t pic_launch_current_units(StoreDesc* d_stores, int nstores, hipStream_
 }
 
 hipError_t pic_launch_yee_step(const InstDesc* d_inst, int ninst, int max_tiles, int dim, bool cart, bool cyl,
-                               bool window, bool march, bool tiles, int parity, hipStream_t st) {
-  const dim3 grid(max_tiles, ninst);
+                               bool window, bool march, bool tiles, int parity, const StoreDesc* d_plan, int nplan,
+                               hipStream_t st) {
+  // the first launch of the group carries the planner's blocks
+  int npx = (nplan + ninst - 1) / ninst;
+  auto launch = [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, dim3(max_tiles + npx, ninst), dim3(kBlock), 0, st, d_inst, parity, d_plan, nplan, npx);
+    npx = 0;
+  };
   if (dim == 2) {
-    if (cart && window) hipLaunchKernelGGL((yee_step<2, true>), grid, dim3(kBlock), 0, st, d_inst, parity);
-    if (cart && !window) hipLaunchKernelGGL((yee_step<2, false>), grid, dim3(kBlock), 0, st, d_inst, parity);
-    if (cyl) hipLaunchKernelGGL(yee_step_rz, grid, dim3(kBlock), 0, st, d_inst, parity);
+    if (cart && window) launch(yee_step<2, true>);
+    if (cart && !window) launch(yee_step<2, false>);
+    if (cyl) launch(yee_step_rz);
   } else if (window) {
-    hipLaunchKernelGGL((yee_step<3, true>), grid, dim3(kBlock), 0, st, d_inst, parity);
+    launch(yee_step<3, true>);
   } else {
-    if (march) hipLaunchKernelGGL(yee_march3, grid, dim3(kBlock), 0, st, d_inst, parity);
-    if (tiles) hipLaunchKernelGGL((yee_step<3, false>), grid, dim3(kBlock), 0, st, d_inst, parity);
+    if (march) launch(yee_march3);
+    if (tiles) launch(yee_step<3, false>);
   }
   return hipGetLastError();
 }

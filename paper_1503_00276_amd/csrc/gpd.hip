@@ -416,6 +416,21 @@ struct BoxWalk {
 // Periodic wrap, cheap when the index is already inside.
 __device__ __forceinline__ int wrap_fast(int v, int n) { return (unsigned)v < (unsigned)n ? v : pic_wrap(v, n); }
 
+// Last step of a sort cycle: add the item's counts of every rebin slot to the
+// destination tiles' totals; the old total is where the item's particles of
+// that slot go inside the tile's range.  Items meet in any order, which only
+// permutes a tile's storage.  The old total is stored by moves_done, after
+// the deposit, so that nothing waits for the atomics in between.
+__device__ __forceinline__ int moves_add(const StoreDesc& S, int tile, const int* scnt) {
+  const int sl = threadIdx.x;
+  const int n = sl < PIC_NSLOT ? scnt[sl] : 0;
+  return n > 0 ? atomicAdd(&S.dcount[S.ndst[tile * PIC_NSLOT + sl]], n) : -1;
+}
+
+__device__ __forceinline__ void moves_done(const StoreDesc& S, int ii, int at) {
+  if (at >= 0) S.pre[ii * PIC_NSLOT + threadIdx.x] = at;
+}
+
 // ---------------------------------------------------------------------------
 // one work item
 // ---------------------------------------------------------------------------
@@ -484,9 +499,10 @@ __device__ __forceinline__ void dep3_comp(Acc* J, int cb, const int st[3], const
 // 6 for strides read at run time.  Mode 7 is the two-phase periodic 2D
 // kernel (process_item2) for FP32 accumulation with Esirkepov's deposit.
 // kstep: steps done since the last rebin check (0 for the first step of a
-// sort cycle).
+// sort cycle).  count: the step's rebin check follows, so the particles are
+// counted by destination tile (the other steps of a cycle skip that).
 template <int DIM, int ORDER, int MODE>
-__device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii, int jp, int kstep, float* smem,
+__device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii, int jp, int kstep, bool count, float* smem,
                              int* scnt) {
   constexpr int NG = ORDER + 1;  // gather taps per axis
   constexpr int W = ORDER + 2;   // deposit window per axis
@@ -629,7 +645,7 @@ __device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii,
   int wo = 0;
   bool wshift = false;
   if (win) {
-    const WinCtl wc = *S.win;
+    const WinCtl wc = S.win[jp];
     wo = wc.origin;
     wshift = pic_win_shifts(g.wa, wc.step + 1) > pic_win_shifts(g.wa, wc.step);
   }
@@ -1034,7 +1050,7 @@ __device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii,
       dead = dead || cc[1] + mv[1] >= g.nx[1];
       died = died || dead;
     }
-    {
+    if (count) {
       // wave-aggregated count per slot (almost every particle is in slot 13)
       const int sl = dead ? -1 : pic_slot(dd[0], dd[1], dd[2]);
       unsigned long long todo = __ballot(sl >= 0);
@@ -1061,7 +1077,7 @@ __device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii,
     if (any_strayed) S.ctl->flag = 1;
     if (any_bad) S.ctl->bad = 1;
   }
-  if (tid < PIC_NSLOT) S.cnt[ii * PIC_NSLOT + tid] = scnt[tid];
+  const int moves = count ? moves_add(S, it.tile, scnt) : -1;
 
   // 4. fold the LDS current into the global current (periodic wrap): FP32
   // atomics of the sums times the unit, or int64 atomics of the sums
@@ -1103,6 +1119,7 @@ __device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii,
       }
     }
   }
+  moves_done(S, ii, moves);
   __syncthreads();
 }
 
@@ -1200,7 +1217,7 @@ __device__ __forceinline__ void interleave_slots(const int (&key)[kSplitR], int 
 // tiles take (every shape order, stray bound 1), as compile-time constants,
 // so that the taps and adds address LDS through instruction offsets.
 template <int ORDER, bool FIXED, typename Acc>
-__device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii, int jp, int kstep, float* smem,
+__device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii, int jp, int kstep, bool count, float* smem,
                               int* scnt, float* sred) {
   constexpr bool kWide = sizeof(Acc) == 8;
   constexpr int NG = ORDER + 1;  // gather taps per axis
@@ -1459,7 +1476,7 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
         bmax = fmaxf(bmax, fabsf(pw[r]) * (sqrtf(uu2) * gi));
       }
     }
-    {
+    if (count) {
       // wave-aggregated count per rebin slot (almost every particle is in slot 13)
       const int slt = live ? pic_slot(dd[0], dd[1], dd[2]) : -1;
       unsigned long long todo = __ballot(slt >= 0);
@@ -1512,7 +1529,7 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
     if (any_strayed) S.ctl->flag = 1;
     if (any_bad) S.ctl->bad = 1;
   }
-  if (tid < PIC_NSLOT) S.cnt[ii * PIC_NSLOT + tid] = scnt[tid];
+  const int moves = count ? moves_add(S, it.tile, scnt) : -1;
   __syncthreads();
 
   // 4. phase B: ISIS ordering average in Esirkepov's closed form, core of the
@@ -1564,6 +1581,7 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
   }
   __syncthreads();
 
+  moves_done(S, ii, moves);
   // 5. fold the tile into the global current (periodic wrap); the int64 mode
   // sums in the instance's own fixed point, so its global sums stay order-free
   const float qinv = ldexpf(1.0f, -e_item);
@@ -1613,7 +1631,7 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
 constexpr int kSplitR2 = 4;  // particles per thread per 2D work item
 
 template <int ORDER>
-__device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii, int jp, int kstep, float* smem,
+__device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii, int jp, int kstep, bool count, float* smem,
                               int* scnt, float* sred) {
   constexpr int NG = ORDER + 1;  // gather taps per axis
   constexpr int W = ORDER + 2;   // deposit window per axis
@@ -1847,7 +1865,7 @@ __device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii
       sv3[r] = pw[r] * uz * gi;
       bmax = fmaxf(bmax, fabsf(pw[r]) * (sqrtf(uu2) * gi));
     }
-    {
+    if (count) {
       // wave-aggregated count per rebin slot (almost every particle is in slot 13)
       const int slt = live ? pic_slot(dd[0], dd[1], 0) : -1;
       unsigned long long todo = __ballot(slt >= 0);
@@ -1877,7 +1895,7 @@ __device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii
     if (any_strayed) S.ctl->flag = 1;
     if (any_bad) S.ctl->bad = 1;
   }
-  if (tid < PIC_NSLOT) S.cnt[ii * PIC_NSLOT + tid] = scnt[tid];
+  const int moves = count ? moves_add(S, it.tile, scnt) : -1;
   __syncthreads();
 
   // 4. phase B: ISIS ordering average in Esirkepov's closed form (2D3V): the
@@ -1981,6 +1999,7 @@ __device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii
   }
   __syncthreads();
 
+  moves_done(S, ii, moves);
   // 5. fold the tile into the global current (periodic wrap), one rounding
   // of each node's sum
   const float qinv = ldexpf(1.0f, -e_item);
@@ -2000,7 +2019,7 @@ __device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii
 }
 
 template <int DIM, int ORDER, int MODE>
-__device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, int nstores, int jp, int kstep) {
+__device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, int nstores, int jp, int kstep, bool count) {
   // 16-byte aligned: the int64 current tile inside it takes 8-byte LDS atomics
   extern __shared__ __align__(16) float smem[];
   __shared__ int s_pref[kMaxGroup + 1];
@@ -2047,12 +2066,12 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
     it.begin = __builtin_amdgcn_readfirstlane(it.begin);
     it.end = __builtin_amdgcn_readfirstlane(it.end);
     if constexpr (MODE == 7)
-      process_item2<ORDER>(S, cur, it, ii, jp, kstep, smem, s_cnt, s_red);
+      process_item2<ORDER>(S, cur, it, ii, jp, kstep, count, smem, s_cnt, s_red);
     else if constexpr (MODE >= 4)
       process_item3<ORDER, MODE == 5, typename std::conditional<MODE == 4, acc_t, unsigned>::type>(
-          S, cur, it, ii, jp, kstep, smem, s_cnt, s_red);
+          S, cur, it, ii, jp, kstep, count, smem, s_cnt, s_red);
     else
-      process_item<DIM, ORDER, MODE>(S, cur, it, ii, jp, kstep, smem, s_cnt);
+      process_item<DIM, ORDER, MODE>(S, cur, it, ii, jp, kstep, count, smem, s_cnt);
   }
   (void)lo;
 }
@@ -2068,8 +2087,8 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
 template <int DIM, int ORDER, int MODE>
 __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(DIM == 2 && ORDER <= 2 && MODE == 0 ? 5 : (MODE == 4 && ORDER == 3 ? 3 : (MODE >= 4 ? 4 : 1))))) gpd_kernel(const StoreDesc* __restrict__ stores, int nstores, int jp,
-                                                     int kstep) {
-  gpd_body<DIM, ORDER, MODE>(stores, nstores, jp, kstep);
+                                                     int kstep, bool count) {
+  gpd_body<DIM, ORDER, MODE>(stores, nstores, jp, kstep, count);
 }
 
 template <int DIM, int ORDER, int MODE>
@@ -2083,14 +2102,14 @@ hipError_t prepare_mode(size_t lds) {
 }
 
 template <int DIM, int ORDER, int MODE>
-void launch_mode(const StoreDesc* stores, int nstores, int grid, size_t lds, int jp, int kstep, hipStream_t st,
+void launch_mode(const StoreDesc* stores, int nstores, int grid, size_t lds, int jp, int kstep, bool count, hipStream_t st,
                  hipEvent_t ev0, hipEvent_t ev1) {
   if (ev0 || ev1)
     // the command processor stamps the events at the kernel's own start and end
     hipExtLaunchKernelGGL(gpd_kernel<DIM, ORDER, MODE>, dim3(grid), dim3(kBlock), (std::uint32_t)lds, st, ev0, ev1, 0,
-                          stores, nstores, jp, kstep);
+                          stores, nstores, jp, kstep, count);
   else
-    gpd_kernel<DIM, ORDER, MODE><<<dim3(grid), dim3(kBlock), lds, st>>>(stores, nstores, jp, kstep);
+    gpd_kernel<DIM, ORDER, MODE><<<dim3(grid), dim3(kBlock), lds, st>>>(stores, nstores, jp, kstep, count);
 }
 
 template <int DIM, int ORDER>
@@ -2110,28 +2129,28 @@ hipError_t prepare_one(int mode, size_t lds) {
 }
 
 template <int DIM, int ORDER>
-hipError_t launch_one(int mode, const StoreDesc* stores, int nstores, int grid, size_t lds, int jp, int kstep,
+hipError_t launch_one(int mode, const StoreDesc* stores, int nstores, int grid, size_t lds, int jp, int kstep, bool count,
                       hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if (mode == 1)
-    launch_mode<DIM, ORDER, 1>(stores, nstores, grid, lds, jp, kstep, st, ev0, ev1);
+    launch_mode<DIM, ORDER, 1>(stores, nstores, grid, lds, jp, kstep, count, st, ev0, ev1);
   else if (mode == 0)
-    launch_mode<DIM, ORDER, 0>(stores, nstores, grid, lds, jp, kstep, st, ev0, ev1);
+    launch_mode<DIM, ORDER, 0>(stores, nstores, grid, lds, jp, kstep, count, st, ev0, ev1);
   else if constexpr (DIM == 2) {
     if (mode == 2)
-      launch_mode<DIM, ORDER, 2>(stores, nstores, grid, lds, jp, kstep, st, ev0, ev1);
+      launch_mode<DIM, ORDER, 2>(stores, nstores, grid, lds, jp, kstep, count, st, ev0, ev1);
     else if (mode == 3)
-      launch_mode<DIM, ORDER, 3>(stores, nstores, grid, lds, jp, kstep, st, ev0, ev1);
+      launch_mode<DIM, ORDER, 3>(stores, nstores, grid, lds, jp, kstep, count, st, ev0, ev1);
     else if (mode == 7)
-      launch_mode<DIM, ORDER, 7>(stores, nstores, grid, lds, jp, kstep, st, ev0, ev1);
+      launch_mode<DIM, ORDER, 7>(stores, nstores, grid, lds, jp, kstep, count, st, ev0, ev1);
     else
       return hipErrorInvalidValue;
   } else {
     if (mode == 4)
-      launch_mode<DIM, ORDER, 4>(stores, nstores, grid, lds, jp, kstep, st, ev0, ev1);
+      launch_mode<DIM, ORDER, 4>(stores, nstores, grid, lds, jp, kstep, count, st, ev0, ev1);
     else if (mode == 5)
-      launch_mode<DIM, ORDER, 5>(stores, nstores, grid, lds, jp, kstep, st, ev0, ev1);
+      launch_mode<DIM, ORDER, 5>(stores, nstores, grid, lds, jp, kstep, count, st, ev0, ev1);
     else if (mode == 6)
-      launch_mode<DIM, ORDER, 6>(stores, nstores, grid, lds, jp, kstep, st, ev0, ev1);
+      launch_mode<DIM, ORDER, 6>(stores, nstores, grid, lds, jp, kstep, count, st, ev0, ev1);
     else
       return hipErrorInvalidValue;
   }
@@ -2288,15 +2307,15 @@ int pic_gpd_resident(int dim, int order, int mode, size_t lds) {
 }
 
 hipError_t pic_launch_gpd(int dim, int order, int mode, const StoreDesc* d_stores, int nstores, int grid,
-                          size_t lds, int parity, int kstep, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                          size_t lds, int parity, int kstep, bool count, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if (dim == 2) {
-    if (order == 1) return launch_one<2, 1>(mode, d_stores, nstores, grid, lds, parity, kstep, st, ev0, ev1);
-    if (order == 2) return launch_one<2, 2>(mode, d_stores, nstores, grid, lds, parity, kstep, st, ev0, ev1);
-    if (order == 3) return launch_one<2, 3>(mode, d_stores, nstores, grid, lds, parity, kstep, st, ev0, ev1);
+    if (order == 1) return launch_one<2, 1>(mode, d_stores, nstores, grid, lds, parity, kstep, count, st, ev0, ev1);
+    if (order == 2) return launch_one<2, 2>(mode, d_stores, nstores, grid, lds, parity, kstep, count, st, ev0, ev1);
+    if (order == 3) return launch_one<2, 3>(mode, d_stores, nstores, grid, lds, parity, kstep, count, st, ev0, ev1);
   } else if (dim == 3) {
-    if (order == 1) return launch_one<3, 1>(mode, d_stores, nstores, grid, lds, parity, kstep, st, ev0, ev1);
-    if (order == 2) return launch_one<3, 2>(mode, d_stores, nstores, grid, lds, parity, kstep, st, ev0, ev1);
-    if (order == 3) return launch_one<3, 3>(mode, d_stores, nstores, grid, lds, parity, kstep, st, ev0, ev1);
+    if (order == 1) return launch_one<3, 1>(mode, d_stores, nstores, grid, lds, parity, kstep, count, st, ev0, ev1);
+    if (order == 2) return launch_one<3, 2>(mode, d_stores, nstores, grid, lds, parity, kstep, count, st, ev0, ev1);
+    if (order == 3) return launch_one<3, 3>(mode, d_stores, nstores, grid, lds, parity, kstep, count, st, ev0, ev1);
   }
   return hipErrorInvalidValue;
 }

@@ -51,7 +51,7 @@ struct GridDesc {
 };
 
 // Control words of one particle store.  The buffer set holding the particles
-// is cur ^ pending: the rebin's fold kernel (one workgroup per store, so no
+// is cur ^ pending: the rebin's planner (one workgroup per store, so no
 // atomics are needed) folds pending into cur when it next runs, and sets
 // pending when it plans a rebin whose scatter fills the other set.
 struct StoreCtl {
@@ -74,11 +74,12 @@ struct StoreCtl {
 
 __host__ __device__ inline int pic_cur(const StoreCtl& c) { return c.cur ^ c.pending; }
 
-// Moving-window state of one instance.  The grid and the particles' cell
-// indices are kept in ring coordinates along x1: ring column r holds window
-// column (r - origin) mod nx1, so a shift only advances the origin, zeroes
-// the old back column (the new front) and refills it.  Kernels read the
-// state at launch; the step's last kernel advances it.
+// Moving-window state of one instance, one entry per step parity.  The grid
+// and the particles' cell indices are kept in ring coordinates along x1: ring
+// column r holds window column (r - origin) mod nx1, so a shift only advances
+// the origin, zeroes the old back column (the new front) and refills it.
+// Every kernel of step n reads entry n & 1; the field step writes the
+// advanced state to the other entry, which nothing else of the step reads.
 struct WinCtl {
   long long step;     // steps done
   int shifts;         // cell shifts done
@@ -102,6 +103,22 @@ struct Item {
   int tile, begin, end, pad;
 };
 
+// A tile's particles are split into work items of at most 'chunk' particles
+// and of equal size (whole wavefronts), so that a tile a little over the chunk
+// does not leave an item of a few particles that stages the tile's fields for
+// itself.  Item k holds [k size, (k + 1) size) of the tile.
+__host__ __device__ inline int pic_item_size(int count, int chunk) {
+  const int ni = (count + chunk - 1) / chunk;
+  if (ni <= 1) return chunk;
+  const int even = ((count + ni - 1) / ni + 63) & ~63;
+  return even < chunk ? even : chunk;
+}
+
+__host__ __device__ inline int pic_item_count(int count, int chunk) {
+  const int size = pic_item_size(count, chunk);
+  return (count + size - 1) / size;
+}
+
 // One particle species of one instance: SoA particles in two ping-pong sets.
 struct StoreDesc {
   GridDesc g;
@@ -122,21 +139,19 @@ struct StoreDesc {
   int* toff[2];              // tile offsets [ntiles+1]
   int* ioff[2];              // first item of each tile [ntiles+1]
   Item* items[2];
-  int* cnt;                  // [max_items][27] slot counts of the current items
-  int* pre;                  // [max_items][27] prefix of cnt over earlier items of the tile
-  int* tot;                  // [ntiles][27]
-  int* dbase;                // [ntiles][27] slot base inside the destination tile
-  int* dcount;               // [ntiles]
+  int* pre;                  // [max_items][27] first place, inside the destination tile's range, of
+                             // the particles of each current item that move to the slot's tile
+  int* dcount;               // [ntiles] particles bound for each tile, counted by the fused kernel in
+                             // the last step of a sort cycle; zero otherwise
   int* bsum;                 // [nblk][2] particles and items of each block of kRebinTiles tiles
   int* bpre;                 // [nblk][2] their exclusive prefix
   int tile0, blk0;           // first tile and tile block of this store within its launch group
   int cap;                   // particles the buffer sets hold
-  WinCtl* win;               // moving window state of the instance (null without a window)
+  const WinCtl* win;         // moving window state of the instance (null without a window)
   int inj_ppc[3];            // moving window: injected particles per cell per axis
   float inj_w;               // moving window: weight of an injected particle
   double inj_uth;            // moving window: thermal spread of the injected momenta (0: at rest)
   unsigned long long inj_seed;  // moving window: seed of their generator
-  const int* nsrc;           // [ntiles][27] tile - delta_s (periodic), per instance
   const int* ndst;           // [ntiles][27] tile + delta_s (periodic), per instance
   StoreCtl* ctl;
   const float* emax;         // the instance's running bound on |E_c| (see InstDesc)

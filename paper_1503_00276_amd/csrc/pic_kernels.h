@@ -29,34 +29,44 @@ hipError_t pic_gpd_prepare(int dim, int order, int mode, size_t lds);
 // bytes of dynamic LDS (after pic_gpd_prepare)
 int pic_gpd_resident(int dim, int order, int mode, size_t lds);
 // kstep: steps done since the last rebin check (bounds the staged halo);
+// count: the step's rebin check follows (the particles are counted by
+// destination tile);
 // ev0 / ev1 (may be null): events stamped at the kernel's start / end
 hipError_t pic_launch_gpd(int dim, int order, int mode, const StoreDesc* d_stores, int nstores, int grid,
-                          size_t lds, int parity, int kstep, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
+                          size_t lds, int parity, int kstep, bool count, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 
 // Yee field solve (field.hip); instances in d_inst[0..ninst)
 int pic_yee_tiles(int dim, const int nx[3], bool window);
 // whether a periodic 3D box takes the field step that marches along z
 bool pic_yee_marches(const int nx[3]);
-hipError_t pic_launch_window_advance(const InstDesc* d_inst, int ninst, hipStream_t st);
 hipError_t pic_launch_smooth_pass(const InstDesc* d_inst, int ninst, int max_ncell, int axis, int lev,
                                   int parity, hipStream_t st);
 // cart / cyl: the group holds Cartesian / r-z instances (each kernel skips the
 // others); window: some instance has a moving window (selects the variant
 // with the window terms); march / tiles: without a window, the group holds 3D
-// boxes that march along z / that take the 3D tiles
+// boxes that march along z / that take the 3D tiles.  The launch also advances
+// the moving windows and, with nplan > 0, plans the rebin check of the nplan
+// stores at d_plan (those of at most pic_plan_tiles() tiles).
 // Per store: this step's fixed point of the one-phase kernels' FP32 current
 // (from the store's bound on |u| and the instance's bound on |E_c|).
 hipError_t pic_launch_current_units(StoreDesc* d_stores, int nstores, hipStream_t st);
 hipError_t pic_launch_yee_step(const InstDesc* d_inst, int ninst, int max_tiles, int dim, bool cart, bool cyl,
-                               bool window, bool march, bool tiles, int parity, hipStream_t st);
+                               bool window, bool march, bool tiles, int parity, const StoreDesc* d_plan, int nplan,
+                               hipStream_t st);
 
-// tile rebin (sort.hip); stores in d_stores[0..nstores)
+// tile rebin (sort.hip); stores in d_stores[0..nstores), after the field step
+// of the same parity, which planned the stores of at most pic_plan_tiles()
+// tiles; big: some store has more; inject_max: most particles a store injects
+// per window shift, thermal: some of them with thermal momenta
+int pic_plan_tiles();
 hipError_t pic_launch_rebin(const StoreDesc* d_stores, int nstores, int max_items, int total_tiles,
-                            int total_blocks, int inject_max, hipStream_t st);
+                            int total_blocks, bool big, int inject_max, bool thermal, int parity,
+                            hipStream_t st);
 
 // diagnostics (diag.hip)
-// adds a species' charge density; kstep: steps done since the last rebin check
-hipError_t pic_launch_rho64(const StoreDesc* d_store, const GridDesc& g, int max_items, int kstep, double* rho,
+// adds a species' charge density; kstep: steps done since the last rebin
+// check, par: parity of the steps done
+hipError_t pic_launch_rho64(const StoreDesc* d_store, const GridDesc& g, int max_items, int kstep, int par, double* rho,
                             hipStream_t st);
 hipError_t pic_launch_fill64(double* p, double v, size_t n, hipStream_t st);
 // r-z: rho = ion + folded charge / (r_j/dr) on rows j >= 1, row 0 = row 1
@@ -64,7 +74,7 @@ hipError_t pic_launch_rz_rho_finish(double* rho, int nz, int nr, double ion, hip
 hipError_t pic_launch_gauss64(const InstDesc* d_inst, const double* rho, double* G, int ncell, int dim,
                               int fpar, hipStream_t st);
 hipError_t pic_launch_charge64(const InstDesc* d_inst, const double* rho0, const double* rho1,
-                               double* C, int ncell, int dim, hipStream_t st);
+                               double* C, int ncell, int dim, int par, hipStream_t st);
 // compensated FP64 sums: out[0..nout) with partial scratch (>= 2*nout*pic_reduce_blocks() doubles)
 int pic_reduce_blocks();
 hipError_t pic_launch_field_sums(const InstDesc* d_inst, int ncell, int fpar, double* scratch, double* out,

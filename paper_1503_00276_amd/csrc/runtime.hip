@@ -54,8 +54,7 @@ struct Instance {
   float* Jsm[2] = {nullptr, nullptr};  // smoothing buffers (only when smoothing is on)
   WinCtl* win = nullptr;               // moving window state (device)
   float* emax = nullptr;               // running bound on |E_c| (device, see InstDesc)
-  int* nsrc = nullptr;  // neighbour tile tables of the rebin
-  int* ndst = nullptr;
+  int* ndst = nullptr;  // neighbour tile table of the rebin
   double wmax[PIC_MAX_SPECIES] = {0, 0, 0, 0, 0, 0, 0, 0};
   double* rho_snap = nullptr;
   bool have_snap = false;
@@ -70,6 +69,8 @@ struct Group {
   int sm_max[3];  // most smoothing passes of any instance, per axis
   int inject_max; // moving window: most particles a store injects per shift
   bool window;    // some instance has a moving window
+  bool thermal = false;  // stores: some moving window injects thermal momenta
+  bool big = false;    // stores: some store has more tiles than the field step's launch plans
   bool units = false;  // stores: some store takes a per-step current unit (current_units)
   int mode = 0;   // stores: boundary logic of the fused kernel (0 periodic, 1 moving window, 2 r-z)
   int resident = 1;  // stores: fused-kernel workgroups resident per CU (the grid is one full wave of them)
@@ -414,11 +415,9 @@ pic_status alloc_species(Sim& S, Instance& I, Species& sp, int64_t cap, int chun
     AL(d.ioff[s], g.ntiles + 1);
     AL(d.items[s], d.max_items);
   }
-  AL(d.cnt, (size_t)d.max_items * PIC_NSLOT);
   AL(d.pre, (size_t)d.max_items * PIC_NSLOT);
-  AL(d.tot, (size_t)g.ntiles * PIC_NSLOT);
-  AL(d.dbase, (size_t)g.ntiles * PIC_NSLOT);
   AL(d.dcount, g.ntiles);
+  HIPCHK(S, hipMemset(d.dcount, 0, (size_t)g.ntiles * sizeof(int)));
   AL(d.bsum, (size_t)2 * ((g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES));
   AL(d.bpre, (size_t)2 * ((g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES));
   AL(sp.ctl, 1);
@@ -430,7 +429,6 @@ pic_status alloc_species(Sim& S, Instance& I, Species& sp, int64_t cap, int chun
     d.Jacc[k] = I.Jacc[k];
     d.J64[k] = I.J64[k];
   }
-  d.nsrc = I.nsrc;
   d.ndst = I.ndst;
   d.cap = (int)cap;
   d.win = I.win;
@@ -473,6 +471,8 @@ pic_status refresh_descriptors(Sim& S) {
           gr.max_blocks += (I.g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES;
           gr.lds = std::max(gr.lds, pic_gpd_lds_bytes(I.g));
           if (I.g.window) gr.window = true;
+          if (I.g.ntiles > pic_plan_tiles()) gr.big = true;
+          if (sp.desc.inj_uth > 0.0) gr.thermal = true;
           if (I.g.acc_mode != PIC_ACC_FIXED64 && !I.g.cyl && !pic_gpd_split(I.g) && !pic_gpd_two_phase2(I.g))
             gr.units = true;
           gr.inject_max = std::max(gr.inject_max, sp.desc.inj_ppc[0] * sp.desc.inj_ppc[1] * sp.desc.inj_ppc[2] *
@@ -661,7 +661,7 @@ pic_status launch_steps(Sim& S, int64_t first, int nsteps, bool end_with_check, 
       const int res = gr.res_k.empty() ? gr.resident : gr.res_k[kk];
       int grid = std::max(1, std::min(gr.max_items, S.num_cu * res));
       HIPCHK(S, pic_launch_gpd(gr.dim, gr.order, gr.mode, S.d_stores + gr.first, gr.count, grid, lds, par,
-                               phase0 + k, S.stream, q == 0 ? p0 : nullptr,
+                               phase0 + k, end_with_check && k == nsteps - 1, S.stream, q == 0 ? p0 : nullptr,
                                q + 1 == S.sgroups.size() ? p1 : nullptr));
     }
     if (p0) S.ev_pending[0].push_back({p0, p1});
@@ -670,20 +670,25 @@ pic_status launch_steps(Sim& S, int64_t first, int nsteps, bool end_with_check, 
       for (int a = 0; a < gr.dim; a++)
         for (int lev = 0; lev < gr.sm_max[a]; lev++)
           HIPCHK(S, pic_launch_smooth_pass(S.d_inst + gr.first, gr.count, gr.max_ncell, a, lev, par, S.stream));
-    for (const Group& gr : S.igroups)
+    const bool check = end_with_check && k == nsteps - 1;
+    for (const Group& gr : S.igroups) {
+      // the group's stores (the store groups are in order of dimension)
+      int first = 0, plan = 0;
+      for (const Group& sg : S.sgroups) {
+        if (sg.dim < gr.dim) first += sg.count;
+        if (check && sg.dim == gr.dim) plan += sg.count;
+      }
       HIPCHK(S, pic_launch_yee_step(S.d_inst + gr.first, gr.count, gr.max_tiles, gr.dim, gr.cart, gr.cyl,
-                                    gr.window, gr.march, gr.tiles3, par, S.stream));
+                                    gr.window, gr.march, gr.tiles3, par, S.d_stores + first, plan, S.stream));
+    }
     prof_end(S, 1, e0);
-    if (end_with_check && k == nsteps - 1) {
+    if (check) {
       e0 = prof_begin(S);
       for (const Group& gr : S.sgroups)
         HIPCHK(S, pic_launch_rebin(S.d_stores + gr.first, gr.count, gr.max_items, gr.max_tiles, gr.max_blocks,
-                                   gr.inject_max, S.stream));
+                                   gr.big, gr.inject_max, gr.thermal, par, S.stream));
       prof_end(S, 2, e0);
     }
-    // moving windows: count the step, move the window when it is due
-    for (const Group& gr : S.igroups)
-      if (gr.window) HIPCHK(S, pic_launch_window_advance(S.d_inst + gr.first, gr.count, S.stream));
   }
   return PIC_OK;
 }
@@ -743,7 +748,7 @@ pic_status sim_step(Sim& S, int64_t nsteps) {
 pic_status read_win(Sim& S, const Instance& I, WinCtl& w) {
   memset(&w, 0, sizeof w);
   if (!I.win) return PIC_OK;
-  HIPCHK(S, hipMemcpy(&w, I.win, sizeof w, hipMemcpyDeviceToHost));
+  HIPCHK(S, hipMemcpy(&w, I.win + (S.steps & 1), sizeof w, hipMemcpyDeviceToHost));
   return PIC_OK;
 }
 
@@ -873,7 +878,8 @@ void bin_particles(const GridDesc& g, int chunk, const HostParticles& h, Binned&
   for (int t = 0; t < g.ntiles; t++) {
     int c = toff[t + 1] - toff[t];
     B.ioff[t] = (int)B.items.size();
-    for (int b = 0; b < c; b += chunk) B.items.push_back(Item{t, toff[t] + b, toff[t] + std::min(c, b + chunk), 0});
+    const int size = pic_item_size(c, chunk);
+    for (int b = 0; b < c; b += size) B.items.push_back(Item{t, toff[t] + b, toff[t] + std::min(c, b + size), 0});
   }
   B.ioff[g.ntiles] = (int)B.items.size();
 }
@@ -1063,7 +1069,7 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
   set_current_scale(I);
   if (win) {
     wc.next_id += n;
-    HIPCHK(S, hipMemcpy(I.win, &wc, sizeof wc, hipMemcpyHostToDevice));
+    HIPCHK(S, hipMemcpy(I.win + (S.steps & 1), &wc, sizeof wc, hipMemcpyHostToDevice));
   }
   st = upload_binned(S, I, sp, h);
   if (st == PIC_OK && (win || rz)) {
@@ -1182,8 +1188,8 @@ pic_status compute_rho(Sim& S, int i, double* d_rho) {
     if (!I.sp[s].used || I.sp[s].np == 0) continue;
     int k = store_desc_index(S, i, s);
     if (k < 0) return S.fail(PIC_E_STATE, "species descriptor missing");
-    HIPCHK(S, pic_launch_rho64(S.d_stores + k, I.g, I.sp[s].max_items, (int)(S.steps % S.sort_interval), d_rho,
-                               S.stream));
+    HIPCHK(S, pic_launch_rho64(S.d_stores + k, I.g, I.sp[s].max_items, (int)(S.steps % S.sort_interval),
+                               (int)(S.steps & 1), d_rho, S.stream));
   }
   if (I.g.cyl) HIPCHK(S, pic_launch_rz_rho_finish(d_rho, I.g.nx[0], I.g.nx[1], I.cfg.ion_density, S.stream));
   return PIC_OK;
@@ -1253,7 +1259,7 @@ pic_status sim_diag(Sim& S, int i, pic_diag_kind kind, void* out, size_t out_byt
       double* src = rho;
       if (kind != PIC_DIAG_RHO) {
         if (kind == PIC_DIAG_CHARGE_RESIDUAL)
-          HIPCHK(S, pic_launch_charge64(S.d_inst + ii, I.rho_snap, rho, res, g.ncell, g.dim, S.stream));
+          HIPCHK(S, pic_launch_charge64(S.d_inst + ii, I.rho_snap, rho, res, g.ncell, g.dim, (int)(S.steps & 1), S.stream));
         else
           HIPCHK(S, pic_launch_gauss64(S.d_inst + ii, rho, res, g.ncell, g.dim, (int)(S.steps & 1), S.stream));
         src = res;
@@ -1476,37 +1482,31 @@ pic_status sim_diag_noalloc(Sim& S, int i, pic_diag_kind kind, void* out, size_t
   if (kind == PIC_DIAG_GAUSS_RESIDUAL)
     HIPCHK(S, pic_launch_gauss64(S.d_inst + ii, rho, (double*)out, I.g.ncell, I.g.dim, (int)(S.steps & 1), S.stream));
   else if (kind == PIC_DIAG_CHARGE_RESIDUAL)
-    HIPCHK(S, pic_launch_charge64(S.d_inst + ii, I.rho_snap, rho, (double*)out, I.g.ncell, I.g.dim, S.stream));
+    HIPCHK(S, pic_launch_charge64(S.d_inst + ii, I.rho_snap, rho, (double*)out, I.g.ncell, I.g.dim, (int)(S.steps & 1),
+                                  S.stream));
   HIPCHK(S, hipStreamSynchronize(S.stream));
   return PIC_OK;
 }
 
-// Neighbour tile tables of the rebin: tile t -/+ delta_s for the 27 slots,
+// Neighbour tile table of the rebin: tile t + delta_s for the 27 slots,
 // periodic in tiles.
 pic_status build_tables(Sim& S, Instance& I) {
   const GridDesc& g = I.g;
-  std::vector<int> ns((size_t)g.ntiles * PIC_NSLOT), nd((size_t)g.ntiles * PIC_NSLOT);
+  std::vector<int> nd((size_t)g.ntiles * PIC_NSLOT);
   for (int t = 0; t < g.ntiles; t++) {
     int tc[3];
     pic_tile_coords(g, t, tc);
     for (int sl = 0; sl < PIC_NSLOT; sl++) {
       int dd[3] = {sl % 3 - 1, (sl / 3) % 3 - 1, sl / 9 - 1};
-      int a[3], b[3];
-      for (int d = 0; d < 3; d++) {
-        a[d] = pic_wrap(tc[d] - dd[d], g.ntile[d]);
-        b[d] = pic_wrap(tc[d] + dd[d], g.ntile[d]);
-      }
-      ns[(size_t)t * PIC_NSLOT + sl] = pic_tile_index(g, a[0], a[1], a[2]);
+      int b[3];
+      for (int d = 0; d < 3; d++) b[d] = pic_wrap(tc[d] + dd[d], g.ntile[d]);
       nd[(size_t)t * PIC_NSLOT + sl] = pic_tile_index(g, b[0], b[1], b[2]);
     }
   }
-  if (I.nsrc) (void)hipFree(I.nsrc);
   if (I.ndst) (void)hipFree(I.ndst);
-  I.nsrc = I.ndst = nullptr;
-  if (hipMalloc(&I.nsrc, ns.size() * sizeof(int)) != hipSuccess ||
-      hipMalloc(&I.ndst, nd.size() * sizeof(int)) != hipSuccess)
+  I.ndst = nullptr;
+  if (hipMalloc(&I.ndst, nd.size() * sizeof(int)) != hipSuccess)
     return S.fail(PIC_E_NOMEM, "tile table allocation failed");
-  HIPCHK(S, hipMemcpy(I.nsrc, ns.data(), ns.size() * sizeof(int), hipMemcpyHostToDevice));
   HIPCHK(S, hipMemcpy(I.ndst, nd.data(), nd.size() * sizeof(int), hipMemcpyHostToDevice));
   return PIC_OK;
 }
@@ -1561,8 +1561,8 @@ pic_status sim_create(Sim& S, const pic_config* cfgs, int n, void* stream) {
     if (hipMalloc(&I.emax, sizeof(float)) != hipSuccess) return S.fail(PIC_E_NOMEM, "field bound allocation failed");
     HIPCHK(S, hipMemset(I.emax, 0, sizeof(float)));
     if (I.cfg.move_window) {
-      if (hipMalloc(&I.win, sizeof(WinCtl)) != hipSuccess) return S.fail(PIC_E_NOMEM, "window state allocation failed");
-      HIPCHK(S, hipMemset(I.win, 0, sizeof(WinCtl)));
+      if (hipMalloc(&I.win, 2 * sizeof(WinCtl)) != hipSuccess) return S.fail(PIC_E_NOMEM, "window state allocation failed");
+      HIPCHK(S, hipMemset(I.win, 0, 2 * sizeof(WinCtl)));
     }
     int npass = 0;
     for (int a = 0; a < I.cfg.ndim; a++) npass += I.cfg.smooth_level[a];
@@ -1624,7 +1624,6 @@ void sim_destroy(Sim& S) {
       if (I.Jsm[k]) (void)hipFree(I.Jsm[k]);
     if (I.win) (void)hipFree(I.win);
     if (I.emax) (void)hipFree(I.emax);
-    if (I.nsrc) (void)hipFree(I.nsrc);
     if (I.ndst) (void)hipFree(I.ndst);
     if (I.rho_snap) (void)hipFree(I.rho_snap);
   }
