@@ -66,11 +66,11 @@ typedef enum {
 /* Accumulation of the current.  Every particle's FP32 contribution is
  * rounded to an integer multiple of a power-of-two unit and the
  * contributions of a tile are summed exactly in integers in LDS.  The unit
- * follows a bound on a single contribution |w| |v|: the work item's largest
- * in the two-phase kernels (periodic 3D; periodic 2D with items of at most
- * 1024 particles), whose 32-bit tile sums hold n such contributions
- * (unit about n 2^-31 of the bound for an item of n particles); a per-step
- * bound of the species in the other kernels, whose tile sums are int64
+ * follows the plasma: in the two-phase kernels (periodic 3D; periodic 2D with
+ * items of at most 1024 particles), whose tile sums are 32-bit, the sum of
+ * |w| |v_d| over the work item (unit 2^-30 of it at most); in the other
+ * kernels, whose tile sums are int64, a per-step bound of the species on a
+ * single contribution |w| |v|
  * (unit 2^-31 of the bound); the instance's 2^-31 max|w| with
  * PIC_ACC_FIXED64. */
 enum {

@@ -236,7 +236,7 @@ __device__ __forceinline__ int cvt_rpi(float x) {
 }
 
 // v is already in units of the fixed point (the instance's, or the work
-// item's in the two-phase 3D kernel; the scale is folded into the
+// item's in the two-phase kernels; the scale is folded into the
 // per-particle prefactors); it is rounded to the nearest unit.
 __device__ __forceinline__ void lds_add(acc_t* p, float v) {
   const int q = cvt_rpi(v);
@@ -254,25 +254,43 @@ __device__ __forceinline__ void lds_add_any(unsigned* p, float v) {
   __hip_atomic_fetch_add(p, (unsigned)cvt_rpi(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Fixed point of one work item's int64 current tile: Q = 2^e with Q b < 2^29
-// for a bound b on any single contribution (a factor 2 to spare for the FP32
-// rounding of the shape differences), so that every contribution converts
-// to an int32; e = 0 when nothing can be deposited.
-__device__ __forceinline__ int item_exponent(float b) {
+// Fixed point of one work item's 32-bit current tile, whose node sums are at
+// most b in magnitude: Q = 2^e with Q b (1 + 2^-12) < 2^31.  b comes from FP32
+// sums, and FP32 rounding lets a contribution exceed its share of b by a few
+// tens of ulps (under 2^-18 relative in all); the rounding of n contributions
+// to the unit adds at most n/2.  A node's sum so stays below 2^31 - 2^18.
+// e = 0 when nothing can be deposited.
+__device__ __forceinline__ int item_exponent32(float b) {
   int ex = 0;
-  (void)frexpf(b, &ex);
-  return b > 0.0f ? min(100, max(-100, 29 - ex)) : 0;
+  (void)frexpf(b * 1.00024414f, &ex);  // b (1 + 2^-12) < 2^ex
+  return b > 0.0f ? min(100, max(-100, 31 - ex)) : 0;
 }
 
-// The same for a 32-bit tile summing at most n contributions per node:
-// Q = 2^e with Q n b (1 + 2^-16) < 2^31.  FP32 rounding lets a contribution
-// exceed its bound b by a few tens of ulps (under 2^-19 relative), and the
-// rounding to the unit adds at most 1/2, so a node's sum of n of them stays
-// below 2^31 - 2^14 in magnitude.
-__device__ __forceinline__ int item_exponent32(float b, int n) {
-  int ex = 0;
-  (void)frexpf((float)n * b * 1.0000153f, &ex);  // n b (1 + 2^-16) < 2^ex
-  return b > 0.0f ? min(100, max(-100, 31 - ex)) : 0;
+// Largest value of the B-spline of an order (at its centre).
+template <int ORDER>
+__device__ constexpr float shape_peak() {
+  return ORDER == 1 ? 1.0f : (ORDER == 2 ? 0.75f : 0.66666669f);
+}
+
+// Sum of N values over the workgroup (every thread calls it, the result is
+// the same in all); sred: N floats per wavefront, read after the caller's
+// next barrier by block_total.
+template <int N>
+__device__ __forceinline__ void block_partial(float (&v)[N], float* sred) {
+#pragma unroll
+  for (int k = 0; k < N; k++) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off);
+    if ((threadIdx.x & 63) == 0) sred[(threadIdx.x >> 6) * N + k] = v[k];
+  }
+}
+
+template <int N>
+__device__ __forceinline__ float block_total(const float* sred, int k) {
+  float t = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; w++) t += sred[w * N + k];
+  return t;
 }
 
 // An int64 node sum times its unit, as FP32.  The low word is taken signed
@@ -1135,25 +1153,25 @@ __device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii,
 // regions carry only the guards the shapes reach (see the host's region
 // guards of this variant).
 //
-// The fixed point of the tile is chosen per work item from the particles
-// just pushed.  A contribution of particle p to one node is at most
-// |w_p| |v_p|: the charge fraction that crosses a face in one step is at most
-// the displacement in cells (the prefix of the shape change along the axis
-// is 1-Lipschitz), and the transverse weight (a time average of products of
-// shape values) is at most one.  With Q = 2^e and Q max_p |w_p| |v_p| < 2^29
-// every contribution converts to an int32 (with a factor 2 to spare for the
-// FP32 rounding of the shape differences) and the int64 sums are exact; the
-// rounding unit follows the item's fastest particle instead of the speed of
-// light, so a slow or cold plasma keeps its relative precision.
+// The fixed point of the tile is chosen per work item from the moves of the
+// particles just pushed.  A node of component d gets at most
+// |w_p| (dx_d / dt) |m_p,d| peak^2 from particle p, m the move in cells: the
+// charge fraction that crosses a face in one step is at most the move (the
+// prefix of the shape change along the axis is 1-Lipschitz), and the
+// transverse weight is a time average of products of two shape values, each
+// at most the spline's peak (1, 3/4, 2/3).  A node's sum is therefore at most
+// the sum of that over the item, and the largest of the three components'
+// sums sets the unit (item_exponent32) of the 32-bit tile (Acc = unsigned; the
+// deterministic mode sums in int64 in the instance's own unit).  The moves
+// are the ones the deposit sees, offsets rounded to FP32, not v dt: of a
+// plasma slower than an ulp a step, rounding can double the latter.
 //
-// The tile is 32-bit (Acc = unsigned) unless the instance sums its current
-// deterministically in int64.  A node gets at most one contribution per
-// particle of the item, so Q max_p |w_p| |v_p| n < 2^31 (with a small margin
-// for rounding) for an item of n particles keeps the int32 sums exact
-// (item_exponent32): the unit is about 2^-31 n of the largest contribution,
-// 2^-23 for the 256 particles of a 4x4x4 tile at four per cell, the FP32
-// rounding of one such contribution.  A 32-bit tile halves the LDS lane
-// traffic of the adds and drops the sign extension of each one.
+// The unit follows the item's mean speed along an axis; from the number of
+// particles times the largest |w| |v| (what a node could get if every
+// particle moved like the fastest, along the axis, over that node) it is 2.4
+// bits coarser for a thermal plasma, and 0.8 or 1.2 bits more with the
+// quadratic or cubic shape.  A 32-bit tile halves the LDS lane traffic of the
+// adds and drops the sign extension of each one.
 
 constexpr int kSplitR = 3;  // particles per thread per work item
 
@@ -1329,7 +1347,7 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
   // 2. phase A: gather, Boris push, advance; store the new state
   const float h = 0.5f * S.qm * g.dt;
   bool strayed = false, bad = false;
-  float bmax = 0.0f;
+  float bsum[3] = {0.0f, 0.0f, 0.0f};  // |w| |move| per axis
   // kept for the deposit: old and new offsets, the move, the weight and the
   // old cell in current-region coordinates (-1: nothing to deposit); kept
   // for the interleaved store: the new cell, its class (-1: no particle) and
@@ -1473,7 +1491,8 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
         smv[r] = (mv[0] + 1) | ((mv[1] + 1) << 2) | ((mv[2] + 1) << 4);
         sjc[r] = (jlo[2] + l[2]) * js01 + (jlo[1] + l[1]) * js0 + jlo[0] + l[0];
         swq[r] = pw[r];
-        bmax = fmaxf(bmax, fabsf(pw[r]) * (sqrtf(uu2) * gi));
+#pragma unroll
+        for (int d = 0; d < 3; d++) bsum[d] += fabsf(pw[r] * ((float)mv[d] + (en[d] - e[d])));
       }
     }
     if (count) {
@@ -1489,19 +1508,17 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
       }
     }
   }
-  // the item's bound on a single contribution: max of |w| |v| over its particles
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) bmax = fmaxf(bmax, __shfl_xor(bmax, off));
-  if ((tid & 63) == 0) sred[tid >> 6] = bmax;
+  block_partial<3>(bsum, sred);
   const int any_strayed = __syncthreads_or(strayed ? 1 : 0);  // also: phase A done, fields dead
   const int any_bad = __syncthreads_or(bad ? 1 : 0);
   float btop = 0.0f;
-  for (int k = 0; k < (nthr >> 6); k++) btop = fmaxf(btop, sred[k]);
+#pragma unroll
+  for (int d = 0; d < 3; d++) btop = fmaxf(btop, g.cdt[d] * block_total<3>(sred, d));
+  btop *= shape_peak<ORDER>() * shape_peak<ORDER>();
   // (the int64 mode: the instance's own fixed point, as in the one-phase kernel)
   int eg = 0;
   (void)frexpf(g.jscale, &eg);  // jscale = 2^(eg-1)
-  const int e_item = __builtin_amdgcn_readfirstlane(
-      kWide ? (g.acc_mode == 2 ? eg - 1 : item_exponent(btop)) : item_exponent32(btop, it.end - it.begin));
+  const int e_item = __builtin_amdgcn_readfirstlane(kWide ? eg - 1 : item_exponent32(btop));
   const float Q = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, e_item))));
 
   // 3. store the new state at the item's interleaved slots (the LDS of the
@@ -1623,9 +1640,10 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
 // Esirkepov's deposit and FP32 accumulation: phase A stages E and B and
 // pushes every particle of the item (up to kSplitR2 per thread), keeping
 // what the deposit needs in registers; phase B deposits into a 32-bit
-// current tile in the same LDS, in the item's own fixed point
-// (item_exponent32: a contribution to one node is at most |w| |v|, the
-// out-of-plane one |w v_3| times a shape average at most one).  Fields and
+// current tile in the same LDS, in the item's own fixed point (as in 3D: a
+// node gets at most |w| |move| dx/dt times the transverse shape's peak from a
+// particle, the out-of-plane component |w v_3| times the peak's square; the
+// sums over the item bound its nodes).  Fields and
 // current never coexist, so a workgroup needs the larger region, not their
 // sum, and no per-store unit has to be prepared before the launch.
 constexpr int kSplitR2 = 4;  // particles per thread per 2D work item
@@ -1730,7 +1748,7 @@ __device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii
   // 2. phase A: gather, Boris push, advance; store the new state
   const float h = 0.5f * S.qm * g.dt;
   bool strayed = false, bad = false;
-  float bmax = 0.0f;
+  float bsum[3] = {0.0f, 0.0f, 0.0f};  // |w| |move| per axis, |w v_3|
   // kept for the deposit: old and new offsets, the move, the old cell in
   // current-region coordinates (-1: no particle), the weight and w v_3
   float se0[R][2], sen[R][2], swq[R], sv3[R];
@@ -1863,7 +1881,9 @@ __device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii
       sjc[r] = (jlo[1] + l[1]) * JR[0] + jlo[0] + l[0];
       swq[r] = pw[r];
       sv3[r] = pw[r] * uz * gi;
-      bmax = fmaxf(bmax, fabsf(pw[r]) * (sqrtf(uu2) * gi));
+#pragma unroll
+      for (int d = 0; d < 2; d++) bsum[d] += fabsf(pw[r] * ((float)mv[d] + (en[d] - e[d])));
+      bsum[2] += fabsf(sv3[r]);
     }
     if (count) {
       // wave-aggregated count per rebin slot (almost every particle is in slot 13)
@@ -1878,15 +1898,12 @@ __device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii
       }
     }
   }
-  // the item's bound on a single contribution: max of |w| |v| over its particles
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) bmax = fmaxf(bmax, __shfl_xor(bmax, off));
-  if ((tid & 63) == 0) sred[tid >> 6] = bmax;
+  block_partial<3>(bsum, sred);
   const int any_strayed = __syncthreads_or(strayed ? 1 : 0);  // also: phase A done, fields dead
   const int any_bad = __syncthreads_or(bad ? 1 : 0);
-  float btop = 0.0f;
-  for (int k = 0; k < (nthr >> 6); k++) btop = fmaxf(btop, sred[k]);
-  const int e_item = __builtin_amdgcn_readfirstlane(item_exponent32(btop, it.end - it.begin));
+  const float btop = shape_peak<ORDER>() * fmaxf(fmaxf(g.cdt[0] * block_total<3>(sred, 0), g.cdt[1] * block_total<3>(sred, 1)),
+                                                 block_total<3>(sred, 2));
+  const int e_item = __builtin_amdgcn_readfirstlane(item_exponent32(btop));
   const float Q = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, e_item))));
 
   // 3. clear the current tile over the dead field tile
@@ -2025,7 +2042,7 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
   __shared__ int s_pref[kMaxGroup + 1];
   __shared__ int s_cur[kMaxGroup];
   __shared__ int s_cnt[PIC_NSLOT];
-  __shared__ float s_red[kBlock / 64];
+  __shared__ float s_red[3 * (kBlock / 64)];
   if (threadIdx.x == 0) {
     int acc = 0;
     for (int s = 0; s < nstores; s++) {
