@@ -100,11 +100,15 @@ typedef struct {
                             used only by the rho and Gauss diagnostics */
   int64_t capacity;      /* maximum particles per species (num_par_max) */
   int32_t tile[3];       /* tile extent in cells; 0 = a default from the grid
-                            (pic_autotune searches it by measurement) */
+                            (periodic 3D boxes: and from the particles per
+                            cell of the first load; pic_autotune searches it
+                            by measurement) */
   int32_t sort_interval; /* steps between rebin checks; 0 = a default from the
                             Courant number (searched by pic_autotune) */
   int32_t chunk;         /* maximum particles one workgroup takes from a tile;
-                            0 = 2048 (searched by pic_autotune); capped at
+                            0 = by the particles loaded, at most 2048 (2048
+                            where a tile is given; searched by
+                            pic_autotune); capped at
                             768 in periodic 3D boxes, and at 1024 in periodic
                             2D ones with FP32 accumulation unless it is asked
                             above 1024 (then the one-phase kernel runs) */

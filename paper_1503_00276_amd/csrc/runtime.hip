@@ -112,6 +112,7 @@ struct Sim {
   bool own_stream = false;
   std::vector<Instance> inst;
   int sort_interval = 1;
+  int64_t total_cells = 0;  // of all instances
   int64_t steps = 0;
   StoreDesc* d_stores = nullptr;
   int d_stores_cap = 0;
@@ -166,15 +167,8 @@ void region_guards(int order, int& fa, int& fb, int& ja, int& jb) {
   else { fa = 2; fb = 3; ja = 2; jb = 4; }
 }
 
-// Largest tile extent <= target along an axis of n cells that divides n and
-// leaves room for a particle to stray 'need' cells; the whole axis otherwise.
-int pick_tile(int n, int target, int need) {
-  if (n <= target) return n;
-  for (int t = target; t >= need; t--)
-    if (n % t == 0) return t;
-  return n;
-}
-
+// Whether tiles of t cells suit an axis of n cells whose particles stray
+// need - 2 cells: the remainder, if any, has to hold them too.
 bool tile_ok(int n, int t, int need) {
   if (t <= 0 || t > n) return false;
   if (t == n) return true;
@@ -183,8 +177,96 @@ bool tile_ok(int n, int t, int need) {
   return r == 0 || r >= need;
 }
 
+// Whether a configuration takes the two-phase periodic 2D kernel: Cartesian
+// boxes without a moving window, with Esirkepov's deposit and FP32
+// accumulation, whose work items fit in it (the library's chunk, or an
+// asked-for chunk of at most what it holds); layouts with larger items keep
+// the one-phase kernel.
+bool two_phase2(const pic_config& c) {
+  return c.ndim == 2 && !c.move_window && c.geometry != PIC_GEOM_RZ && c.deposit == PIC_DEPOSIT_ISIS &&
+         c.accumulator != PIC_ACC_FIXED64 && (c.chunk == 0 || c.chunk <= pic_gpd_two_phase2_chunk());
+}
+
+// Cells per tile of the default layout.  Every work item stages its tile's
+// fields with a halo and folds its current, so tiles are large where there
+// are items enough to fill the chip, and small where there are not.
+//   3D, two-phase kernel: 512 particles per tile, from 64 to 256 cells (ppc is
+//     the mean particles per cell, known at the first load; 0 before).  96^3
+//     cells, us a step with 4x4x4 / 8x4x4 / 8x8x4 tiles: quadratic shape at
+//     1, 2, 4, 8 per cell 295 / 219 / 175, 313 / 242 / 223, 363 / 319 / 350,
+//     522 / 572 / 572; cubic 375 / 267 / 249, 405 / 319 / 330, 483 / 457 / 548,
+//     733 / 837 / 958; linear 222 / 157 / 131 ... 375 / 389 / 387.
+//   2D, two-phase kernel: 1,024 tiles (one wave of workgroups), from 64 to 512
+//     cells: 64x64 8x8 16.7 us, 16x16 17.9; 512x256 at 4 per cell 16x8 32, 16x16
+//     38; 1024x512 at 8 per cell 16x8 155, 16x16 144, 32x16 140.
+//   2D, one-phase kernel: 512 tiles, from 128 to 256 cells.
+//   3D, one-phase kernel: 512 cells.
+// total: cells of all instances, which fill the chip together.
+double default_tile_cells(const GridDesc& g, int64_t total, double ppc) {
+  if (pic_gpd_split(g)) return ppc > 0.0 ? std::min(256.0, std::max(64.0, 512.0 / ppc)) : 64.0;
+  if (g.dim == 3) return 512.0;
+  if (pic_gpd_two_phase2(g)) return std::min(512.0, std::max(64.0, (double)total / 1024.0));
+  return std::min(256.0, std::max(128.0, (double)total / 512.0));
+}
+
+// Default tile: among the extents valid on every axis (the asked-for ones where
+// given) whose LDS leaves room for two workgroups per CU, the shape whose mean
+// volume (an axis of n cells makes ceil(n / t) tiles of n / ceil(n / t) cells
+// on average) is closest to 'cells', x-long in 2D (contiguous field rows), and
+// of multiples of four in 3D (the cells of a wavefront then spread over the LDS
+// banks; the 4x4xN strides are compile-time constants).  Extents that do not
+// divide the axis are taken too: an axis of 37 or 53 cells used to become one
+// tile (45x37x53, linear: 120 us in 3x17x25 tiles, 43 us in 9x8x8).  Returns
+// false when no shape is valid.
+bool default_tile(const GridDesc& g0, const pic_config& c, double cells, int out[3]) {
+  struct Extent {
+    int t;
+    double lg, cost;  // log2 of the mean extent; what the extent itself costs
+  };
+  GridDesc g = g0;
+  std::vector<Extent> cand[3];
+  for (int d = 0; d < 3; d++) {
+    const int need = g.slk[d] + 2, n = g.nx[d];
+    auto add = [&](int t) {
+      double cost = n % t != 0 ? 0.05 : 0.0;
+      if (g.dim == 3 && t % 4 != 0) cost += 0.15;
+      cand[d].push_back({t, std::log2((double)n / ((n + t - 1) / t)), cost});
+    };
+    if (d >= g.dim) {
+      add(1);
+    } else if (c.tile[d] != 0) {
+      if (c.tile[d] > 0) add(c.tile[d]);
+    } else {
+      const int most = g.dim == 3 ? 16 : 64;
+      for (int t = need; t < n && t <= most; t++)
+        if (tile_ok(n, t, need)) add(t);
+      if (n <= most || cand[d].empty()) add(n);
+    }
+  }
+  const double want = std::log2(cells);
+  const double aspect = g.dim == 3 ? 0.0 : (pic_gpd_two_phase2(g) ? (cells >= 192.0 ? 1.6 : 0.5) : 0.0);
+  double best = 1e300;
+  for (const Extent& a : cand[0])
+    for (const Extent& b : cand[1])
+      for (const Extent& e : cand[2]) {
+        double sc = a.cost + b.cost + (g.dim == 3 ? e.cost : 0.0) + std::fabs(a.lg + b.lg + e.lg - want) +
+                    0.1 * std::fabs(a.lg - b.lg - aspect);
+        if (g.dim == 3) sc += 0.1 * std::fabs(b.lg - e.lg) + 0.01 * (e.lg - a.lg);
+        if (sc >= best) continue;
+        g.tile[0] = a.t;
+        g.tile[1] = b.t;
+        g.tile[2] = e.t;
+        if (pic_gpd_split(g)) pic_gpd_split_strides(g);
+        if (pic_gpd_lds_bytes(g) > (size_t)kLdsMax / 2) continue;
+        best = sc;
+        for (int d = 0; d < 3; d++) out[d] = g.tile[d];
+      }
+  return best < 1e300;
+}
+
 // Fill g from a validated configuration, tile and sort interval.
-pic_status setup_grid(Sim& S, const pic_config& c, int sort_interval, GridDesc& g) {
+// ppc: mean particles per cell (0: not known), for the default tile.
+pic_status setup_grid(Sim& S, const pic_config& c, int sort_interval, GridDesc& g, double ppc = 0.0) {
   memset(&g, 0, sizeof g);
   g.dim = c.ndim;
   g.order = c.shape_order;
@@ -221,14 +303,7 @@ pic_status setup_grid(Sim& S, const pic_config& c, int sort_interval, GridDesc& 
     g.slack = std::max(g.slack, g.slk[d]);
   }
   region_guards(g.order, g.fa, g.fb, g.ja, g.jb);
-  // The two-phase periodic 2D kernel takes Cartesian boxes without a moving
-  // window, with Esirkepov's deposit and FP32 accumulation, whose work items
-  // fit in it (the library's chunk, or an asked-for chunk of at most what it
-  // holds); layouts with larger items keep the one-phase kernel.
-  g.tp2 = (c.ndim == 2 && !g.window && !g.cyl && g.deposit == 0 && g.acc_mode != PIC_ACC_FIXED64 &&
-           (c.chunk == 0 || c.chunk <= pic_gpd_two_phase2_chunk()))
-              ? 1
-              : 0;
+  g.tp2 = two_phase2(c) ? 1 : 0;
   if (pic_gpd_split(g)) {
     // the two-phase kernel stages only what the shapes reach, one node less
     // above than the one-phase kernel: gather taps reach cell offsets
@@ -238,6 +313,14 @@ pic_status setup_grid(Sim& S, const pic_config& c, int sort_interval, GridDesc& 
     g.jb -= 1;
   }
   g.ntiles = 1;
+  int auto_tile[3] = {0, 0, 0};
+  bool any_auto = false;
+  for (int d = 0; d < c.ndim; d++) any_auto = any_auto || c.tile[d] == 0;
+  if (any_auto) {
+    const int64_t total = std::max<int64_t>(S.total_cells, (int64_t)g.nx[0] * g.nx[1] * g.nx[2]);
+    if (!default_tile(g, c, default_tile_cells(g, total, ppc), auto_tile))
+      for (int d = 0; d < c.ndim; d++) auto_tile[d] = g.nx[d];  // shrunk below
+  }
   for (int d = 0; d < 3; d++) {
     if (d >= c.ndim) {
       g.tile[d] = 1;
@@ -245,11 +328,7 @@ pic_status setup_grid(Sim& S, const pic_config& c, int sort_interval, GridDesc& 
       continue;
     }
     const int need = g.slk[d] + 2;
-    int t = c.tile[d];
-    // default extents: 16 in 2D; in 3D 4 for the two-phase kernel (a tile of
-    // 4x4x4 cells holds the 256-512 particles of one work item at 4-8 per
-    // cell), 8 otherwise
-    if (t == 0) t = pick_tile(g.nx[d], c.ndim == 2 ? 16 : (pic_gpd_split(g) ? 4 : 8), need);
+    const int t = c.tile[d] != 0 ? c.tile[d] : auto_tile[d];
     if (!tile_ok(g.nx[d], t, need))
       return S.fail(PIC_E_INVALID, "tile[%d]=%d does not suit nx=%d (needs >= %d cells per tile and per remainder)",
                     d, t, g.nx[d], need);
@@ -338,16 +417,53 @@ pic_status validate(Sim& S, const pic_config& c) {
   return PIC_OK;
 }
 
-int default_interval(const pic_config& c) {
+// asked_tiles: some instance's tiles are given; they have to hold what strays
+// in an interval, so the interval then stays short.
+int default_interval(const pic_config& c, bool asked_tiles) {
   // 3D tiles are LDS-bound: keep the slack at one cell and check every step;
   // a moving window removes and injects particles at every step's check, and
   // the r-z wall removes the particles that reach it at the step's check
   if (c.ndim == 3 || c.move_window || c.geometry == PIC_GEOM_RZ) return 1;
   double vmax = 0.0;
   for (int d = 0; d < c.ndim; d++) vmax = std::max(vmax, c.dt / c.dx[d]);
+  if (two_phase2(c) && !asked_tiles) {
+    // field and current tile share the two-phase kernel's LDS, so a wider halo
+    // costs it little and the check and the scatter are spread over more
+    // steps: 1024x256 laser wakefield (0.92 cells a step) at 2 / 4 / 8 / 12
+    // steps 125 / 108 / 104 / 98 us a step, thermal boxes (0.5 cells a step)
+    // at 3 / 8 / 12 41-147 / 41-144 / 42-150; the longest interval up to 8
+    // whose strayed particles fit tiles of 16 cells or less
+    for (int s = 8; s > 1; s--)
+      if (3 + (int)std::ceil((s - 1) * vmax - 1e-12) <= 16) return s;
+    return 1;
+  }
   // largest interval whose slack stays at 2 cells
   int s = 1 + (int)std::floor(1.0 / vmax + 1e-12);
   return std::max(1, std::min(s, 8));
+}
+
+// Particles per work item unless asked for (np: the store's particles).  Small
+// stores are split so that the chip has work for its workgroups, large ones
+// take the items that stage least.
+//   2D, two-phase: 512 items, 256 to 1,024 particles.  64x64 at 16 per cell
+//     256 / 512 / 1,024: 16.7 / 17.6 / 21 us a step; 256x128 at 8 per cell
+//     512 / 1,024 in 16x16 tiles 27 / 30; 1024x512 512 / 1,024: 167 / 144.
+//   2D, one-phase: 256 particles in a store of under 2^18, else 2,048 items
+//     from 512 to 2,048 particles.  r-z 384x96 256 / 512 / 2,048: 53 / 57 / 71 us
+//     a step; moving window 768x192 512 / 1,024 / 2,048: 132 / 135 / 164.
+//   3D: 2,048 (the two-phase kernel takes at most 768 of them).
+// Tiles that were asked for keep the library's largest items.
+int default_chunk(const Sim& S, const pic_config& c, const GridDesc& g, int64_t np) {
+  const int64_t all = np * (int64_t)S.inst.size();  // the instances of a batch run together
+  auto split = [&](int items, int lo, int hi) {
+    const int64_t c = (all / items + 63) / 64 * 64;
+    return (int)std::min<int64_t>(hi, std::max<int64_t>(lo, c));
+  };
+  for (int d = 0; d < g.dim; d++)
+    if (c.tile[d] != 0) return 2048;
+  if (g.dim == 3) return 2048;
+  if (pic_gpd_two_phase2(g)) return split(512, 256, pic_gpd_two_phase2_chunk());
+  return all < (1 << 18) ? 256 : split(2048, 512, 2048);
 }
 
 template <typename T>
@@ -955,6 +1071,25 @@ pic_status copy_in(Sim& S, std::vector<double>& dst, const double* src, size_t n
   return PIC_OK;
 }
 
+pic_status build_tables(Sim& S, Instance& I);
+
+// First load of an instance, before anything is binned: the default tile of a
+// periodic 3D box follows its particles per cell, and the neighbour table is
+// made for the tiles.
+pic_status first_load_tiles(Sim& S, Instance& I, int64_t n) {
+  if (I.ndst) return PIC_OK;
+  bool asked = false;
+  for (int d = 0; d < I.g.dim; d++) asked = asked || I.cfg.tile[d] != 0;
+  if (pic_gpd_split(I.g) && !asked) {
+    GridDesc g;
+    pic_status st = setup_grid(S, I.cfg, S.sort_interval, g, (double)n / I.g.ncell);
+    if (st != PIC_OK) return st;
+    I.g = g;
+    S.dirty = true;
+  }
+  return build_tables(S, I);
+}
+
 pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, const double* x,
                     const double* u, const double* w, uint32_t flags) {
   if (inst < 0 || inst >= (int)S.inst.size()) return S.fail(PIC_E_INVALID, "instance %d out of range", inst);
@@ -979,6 +1114,7 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
   for (double v : hw)
     if (!std::isfinite(v)) return S.fail(PIC_E_RANGE, "non-finite weight");
   const int64_t total = sp.np + n;
+  if ((st = first_load_tiles(S, I, n)) != PIC_OK) return st;
   if (I.cfg.capacity > 0 && total > I.cfg.capacity)
     return S.fail(PIC_E_NOMEM, "species %d would hold %lld particles, capacity %lld", species, (long long)total,
                   (long long)I.cfg.capacity);
@@ -1051,7 +1187,7 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
   }
   if (!sp.used || want > sp.cap) {
     int64_t cap = I.cfg.capacity > 0 ? std::max<int64_t>(I.cfg.capacity, want) : want;
-    int chunk = I.cfg.chunk > 0 ? I.cfg.chunk : 2048;
+    int chunk = I.cfg.chunk > 0 ? I.cfg.chunk : default_chunk(S, I.cfg, I.g, want);
     if ((st = alloc_species(S, I, sp, std::max<int64_t>(cap, 1), chunk)) != PIC_OK) return st;
     sp.used = true;
     sp.rqm = rqm;
@@ -1515,10 +1651,19 @@ pic_status sim_create(Sim& S, const pic_config* cfgs, int n, void* stream) {
   if (!cfgs || n < 1) return S.fail(PIC_E_INVALID, "no configuration");
   // everything that can be checked on the host is checked before any HIP call
   int SI = 0;
+  bool asked_tiles = false;
   for (int i = 0; i < n; i++) {
     pic_status st = validate(S, cfgs[i]);
     if (st != PIC_OK) return st;
-    int si = cfgs[i].sort_interval > 0 ? cfgs[i].sort_interval : default_interval(cfgs[i]);
+    int64_t nc = 1;
+    for (int d = 0; d < cfgs[i].ndim; d++) {
+      nc *= cfgs[i].nx[d];
+      asked_tiles = asked_tiles || cfgs[i].tile[d] != 0;
+    }
+    S.total_cells += nc;
+  }
+  for (int i = 0; i < n; i++) {
+    int si = cfgs[i].sort_interval > 0 ? cfgs[i].sort_interval : default_interval(cfgs[i], asked_tiles);
     SI = (i == 0) ? si : std::min(SI, si);
   }
   for (int i = 0; i < n; i++) {
@@ -1556,7 +1701,6 @@ pic_status sim_create(Sim& S, const pic_config* cfgs, int n, void* stream) {
         return S.fail(PIC_E_NOMEM, "field allocation failed");
       HIPCHK(S, hipMemset(I.F[k], 0, 6 * nc * sizeof(float)));
     }
-    if ((st = build_tables(S, I)) != PIC_OK) return st;
     if (hipMalloc(&I.Jout, 3 * nc * sizeof(float)) != hipSuccess) return S.fail(PIC_E_NOMEM, "current allocation failed");
     if (hipMalloc(&I.emax, sizeof(float)) != hipSuccess) return S.fail(PIC_E_NOMEM, "field bound allocation failed");
     HIPCHK(S, hipMemset(I.emax, 0, sizeof(float)));
