@@ -383,12 +383,17 @@ __global__ void __launch_bounds__(kBlock) sq_sums(const double* x, int n, double
   block_reduce_store<1>(v, partial);
 }
 
-// Export position in cell units (cell + offset), u and w of every particle
-// into row id (load order); the host scales positions by the FP64 cell size.
-// Rows go to their id (ids = 0..np-1), or, with ids != null (moving window:
-// ids have gaps), to their storage index with the id in ids[] (-1 for a
-// removed particle) for the host to sort.
-__global__ void __launch_bounds__(kBlock) export_state(const StoreDesc* __restrict__ sp, double* out, int* ids) {
+// Export position, u and w of every particle into row id (load order).
+// With ids != null (moving window, r-z: ids have gaps) rows go to their storage
+// index with the id in ids[] (-1 for a removed particle) for the host to sort,
+// and positions stay in cell units (cell + offset); else they are scaled,
+// xmin + (cell + offset) dx in separate FP64 roundings.
+struct Scale {
+  double xmin[3], dx[3];
+};
+
+__global__ void __launch_bounds__(kBlock) export_state(const StoreDesc* __restrict__ sp, double* out, int* ids,
+                                                       Scale sc) {
   const StoreDesc& S = *sp;
   const GridDesc& g = S.g;
   const int cur = pic_cur(*S.ctl);
@@ -400,22 +405,15 @@ __global__ void __launch_bounds__(kBlock) export_state(const StoreDesc* __restri
     int c[3];
     pic_unpack(g, cell, c);
     double* row = out + (size_t)(ids ? p : S.id[cur][p]) * stride;
-    for (int d = 0; d < g.dim; d++) row[d] = (double)c[d] + (double)S.eps[cur][d][p];
+    for (int d = 0; d < g.dim; d++) {
+      const double x = (double)c[d] + (double)S.eps[cur][d][p];
+      row[d] = ids ? x : __dadd_rn(sc.xmin[d], __dmul_rn(x, sc.dx[d]));
+    }
     row[g.dim + 0] = S.u[cur][0][p];
     row[g.dim + 1] = S.u[cur][1][p];
     row[g.dim + 2] = S.u[cur][2][p];
     row[g.dim + 3] = S.w[cur][p];
   }
-}
-
-__global__ void f32_to_f64(const float* in, double* out, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    out[i] = in[i];
-}
-
-__global__ void f64_to_f32(const double* in, float* out, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    out[i] = (float)in[i];
 }
 
 int grid_for(size_t n) {
@@ -492,17 +490,13 @@ hipError_t pic_launch_sq_sums(const double* v, int n, double* scratch, double* o
   return hipGetLastError();
 }
 
-hipError_t pic_launch_export_state(const StoreDesc* d_store, int np, double* out, int* ids, hipStream_t st) {
-  hipLaunchKernelGGL(export_state, dim3(grid_for(np)), dim3(kBlock), 0, st, d_store, out, ids);
-  return hipGetLastError();
-}
-
-hipError_t pic_launch_f32_to_f64(const float* in, double* out, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(f32_to_f64, dim3(grid_for(n)), dim3(kBlock), 0, st, in, out, n);
-  return hipGetLastError();
-}
-
-hipError_t pic_launch_f64_to_f32(const double* in, float* out, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(f64_to_f32, dim3(grid_for(n)), dim3(kBlock), 0, st, in, out, n);
+hipError_t pic_launch_export_state(const StoreDesc* d_store, int np, double* out, int* ids, const double* xmin,
+                                   const double* dx, hipStream_t st) {
+  Scale sc{};
+  for (int d = 0; d < 3 && xmin; d++) {
+    sc.xmin[d] = xmin[d];
+    sc.dx[d] = dx[d];
+  }
+  hipLaunchKernelGGL(export_state, dim3(grid_for(np)), dim3(kBlock), 0, st, d_store, out, ids, sc);
   return hipGetLastError();
 }

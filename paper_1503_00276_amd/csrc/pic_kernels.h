@@ -82,6 +82,6 @@ hipError_t pic_launch_field_sums(const InstDesc* d_inst, int ncell, int fpar, do
 hipError_t pic_launch_particle_sums(const StoreDesc* d_store, int np, double rqm, double* scratch,
                                     double* out, hipStream_t st);
 hipError_t pic_launch_sq_sums(const double* v, int n, double* scratch, double* out, hipStream_t st);
-hipError_t pic_launch_export_state(const StoreDesc* d_store, int np, double* out, int* ids, hipStream_t st);
-hipError_t pic_launch_f32_to_f64(const float* in, double* out, size_t n, hipStream_t st);
-hipError_t pic_launch_f64_to_f32(const double* in, float* out, size_t n, hipStream_t st);
+// xmin, dx (3 each): positions scaled to the caller's (null with ids: cell units)
+hipError_t pic_launch_export_state(const StoreDesc* d_store, int np, double* out, int* ids, const double* xmin,
+                                   const double* dx, hipStream_t st);

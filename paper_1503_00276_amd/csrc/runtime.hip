@@ -17,6 +17,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -120,6 +121,11 @@ struct Sim {
   std::vector<Group> sgroups, igroups;
   std::vector<int> store_inst, store_species;  // d_stores index -> (instance, species)
   bool dirty = true;
+  // the control words of every (instance, species), in one array, and the
+  // host's copy: current unless steps were queued or a store was written since
+  StoreCtl* d_ctl = nullptr;
+  std::vector<StoreCtl> h_ctl;
+  bool ctl_current = false;
   double* d_scratch = nullptr;  // reductions
   double* d_out = nullptr;      // reduction outputs
   void* d_diag = nullptr;       // diagnostics' device buffers, kept between calls
@@ -536,9 +542,10 @@ pic_status alloc_species(Sim& S, Instance& I, Species& sp, int64_t cap, int chun
   HIPCHK(S, hipMemset(d.dcount, 0, (size_t)g.ntiles * sizeof(int)));
   AL(d.bsum, (size_t)2 * ((g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES));
   AL(d.bpre, (size_t)2 * ((g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES));
-  AL(sp.ctl, 1);
 #undef AL
+  sp.ctl = S.d_ctl + ((&I - S.inst.data()) * PIC_MAX_SPECIES + (&sp - I.sp));
   d.ctl = sp.ctl;
+  S.ctl_current = false;
   d.F[0] = I.F[0];
   d.F[1] = I.F[1];
   for (int k = 0; k < 2; k++) {
@@ -836,6 +843,7 @@ pic_status sim_step(Sim& S, int64_t nsteps) {
   if (st != PIC_OK) return st;
   if (S.sgroups.empty() && S.igroups.empty()) return PIC_OK;
   const int SI = S.sort_interval;
+  S.ctl_current = false;
   int64_t done = 0;
   while (done < nsteps) {
     int64_t phase = S.steps % SI;  // steps already done in the current cycle
@@ -868,13 +876,26 @@ pic_status read_win(Sim& S, const Instance& I, WinCtl& w) {
   return PIC_OK;
 }
 
+// Host copy of a store's control words (after sim_sync).
+const StoreCtl& host_ctl(const Sim& S, const Species& sp) { return S.h_ctl[sp.ctl - S.d_ctl]; }
+
+// Wait for the stream and bring the host's control words up to date: one copy
+// and one wait for all stores.  (One blocking copy per store made every
+// diagnostic of a 24-instance batch cost 390 us.)
 pic_status sim_sync(Sim& S) {
+  size_t used = 0;  // up to the last species in use
+  if (!S.ctl_current)
+    for (size_t i = 0; i < S.inst.size(); i++)
+      for (size_t s = 0; s < PIC_MAX_SPECIES; s++)
+        if (S.inst[i].sp[s].used && S.inst[i].sp[s].ctl) used = i * PIC_MAX_SPECIES + s + 1;
+  if (used > 0)
+    HIPCHK(S, hipMemcpyAsync(S.h_ctl.data(), S.d_ctl, used * sizeof(StoreCtl), hipMemcpyDeviceToHost, S.stream));
   HIPCHK(S, hipStreamSynchronize(S.stream));
+  S.ctl_current = true;
   for (Instance& I : S.inst)
     for (Species& sp : I.sp) {
       if (!sp.used || !sp.ctl) continue;
-      StoreCtl c{};
-      HIPCHK(S, hipMemcpy(&c, sp.ctl, sizeof c, hipMemcpyDeviceToHost));
+      const StoreCtl& c = host_ctl(S, sp);
       if (c.bad) return S.fail(PIC_E_STATE, "a particle left the region staged for its tile");
       if ((I.cfg.move_window || I.g.cyl) && c.nchecks > 0 && c.np != sp.np) {
         // a moving window removed and injected particles, or the r-z wall
@@ -1035,6 +1056,7 @@ pic_status upload_bins(Sim& S, Species& sp, const Binned& B) {
                                 (double)o.u[2][q] * o.u[2][q]));
   c.umax = std::max(c.umax, std::nextafter((float)(um * (1.0 + 1e-6)), INFINITY));
   HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
+  S.ctl_current = false;
   sp.np = (int64_t)n;
   sp.desc.np = (int)n;
   S.dirty = true;
@@ -1047,17 +1069,22 @@ pic_status upload_binned(Sim& S, Instance& I, Species& sp, const HostParticles& 
   return upload_bins(S, sp, B);
 }
 
-// Run f(0..n-1) on up to 16 host threads.
+// Run f(0..n-1) on up to 'most' host threads, the caller's among them (alone if
+// no other can be started).
 template <class F>
-void parallel_for(int n, F f) {
+void parallel_for(int n, F f, unsigned most = 16) {
   unsigned hc = std::thread::hardware_concurrency();
-  int nt = std::max(1, std::min(n, (int)std::min(16u, hc ? hc : 1u)));
+  const int nt = std::max(1, std::min(n, (int)std::min(most, hc ? hc : 1u)));
   std::atomic<int> next{0};
+  auto work = [&]() {
+    for (int i; (i = next.fetch_add(1)) < n;) f(i);
+  };
   std::vector<std::thread> th;
-  for (int t = 0; t < nt; t++)
-    th.emplace_back([&]() {
-      for (int i; (i = next.fetch_add(1)) < n;) f(i);
-    });
+  try {
+    for (int t = 1; t < nt; t++) th.emplace_back(work);
+  } catch (const std::exception&) {
+  }
+  work();
   for (auto& x : th) x.join();
 }
 
@@ -1218,6 +1245,7 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
     if (win && species == 0 && I.cfg.inject_uth > 0.0)
       c.umax = std::max(c.umax, (float)(8.5718 * std::sqrt(3.0) * I.cfg.inject_uth * (1.0 + 1e-6)));
     HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
+    S.ctl_current = false;
   }
   return st;
 }
@@ -1316,6 +1344,63 @@ pic_status need(Sim& S, size_t want, size_t out_bytes, size_t* written) {
   return PIC_OK;
 }
 
+// Host threads of an export.  A caller's fresh buffer costs a page fault per
+// 4 KiB, more than the copy (9.5 GB/s on one thread against 17 GB/s into pages
+// in use), so large exports fill it from several.
+constexpr unsigned kExportThreads = 8;
+
+// nplane FP32 grid planes to the caller's FP64 array.  The planes cross in
+// FP32, by chunks of rows, and are widened on the host: half the bytes of a
+// conversion on the device, and a chunk is widened while others cross.
+// origin: ring column of window column 0 (moving window; rows are rotated).
+// Six planes of 128x64x64 (25 MB): 4.9 ms before, with the binding's copies.
+pic_status export_planes(Sim& S, const GridDesc& g, const float* d, size_t nplane, int origin, double* out) {
+  const int n0 = g.nx[0];
+  const size_t rows = nplane * (size_t)(g.ncell / n0);
+  const size_t per = std::max<size_t>(1, (size_t)(1 << 18) / n0);
+  const int chunks = (int)((rows + per - 1) / per);
+  std::atomic<int> err{(int)hipSuccess};
+  const std::thread::id caller = std::this_thread::get_id();
+  parallel_for(chunks, [&](int k) {
+    const size_t r0 = (size_t)k * per, nr = std::min(per, rows - r0);
+    std::unique_ptr<float[]> mem(new (std::nothrow) float[nr * n0]);
+    float* buf = mem.get();
+    hipError_t e = buf ? hipSuccess : hipErrorOutOfMemory;
+    // (a new thread starts on device 0)
+    if (e == hipSuccess && std::this_thread::get_id() != caller) e = hipSetDevice(S.device);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(buf, d + r0 * n0, nr * n0 * sizeof(float), hipMemcpyDeviceToHost, S.stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(S.stream);
+    if (e != hipSuccess) {
+      err = (int)e;
+      return;
+    }
+    for (size_t r = 0; r < nr; r++) {
+      const float* src = buf + r * n0;
+      double* dst = out + (r0 + r) * n0;
+      for (int w = 0; w < n0 - origin; w++) dst[w] = src[w + origin];
+      for (int w = n0 - origin; w < n0; w++) dst[w] = src[w + origin - n0];
+    }
+  }, kExportThreads);
+  HIPCHK(S, (hipError_t)err.load());
+  return PIC_OK;
+}
+
+// Device memory to the caller's buffer: the pages of a large one are touched
+// from several threads first (the bytes are overwritten by the copy).
+pic_status export_copy(Sim& S, void* out, const void* d, size_t bytes) {
+  constexpr size_t kPart = (size_t)2 << 20;
+  if (bytes >= 2 * kPart)
+    parallel_for((int)((bytes + kPart - 1) / kPart), [&](int k) {
+      volatile char* p = (volatile char*)out;
+      const size_t end = std::min(bytes, (size_t)(k + 1) * kPart);
+      for (size_t b = (size_t)k * kPart; b < end; b += 4096) p[b] = 0;
+    }, kExportThreads);
+  HIPCHK(S, hipMemcpyAsync(out, d, bytes, hipMemcpyDeviceToHost, S.stream));
+  HIPCHK(S, hipStreamSynchronize(S.stream));
+  return PIC_OK;
+}
+
 pic_status compute_rho(Sim& S, int i, double* d_rho) {
   Instance& I = S.inst[i];
   // r-z: the folded ring charge first, then the ring volumes and the ions
@@ -1349,20 +1434,24 @@ pic_status sim_diag(Sim& S, int i, pic_diag_kind kind, void* out, size_t out_byt
     case PIC_DIAG_MOMENTUM: {
       size_t want = (kind == PIC_DIAG_ENERGY ? 4 : 3) * sizeof(double);
       if ((st = need(S, want, out_bytes, written)) != PIC_OK) return st;
-      double fe[2] = {0, 0}, pm[4] = {0, 0, 0, 0};
-      HIPCHK(S, pic_launch_field_sums(S.d_inst + ii, g.ncell, (int)(S.steps & 1), S.d_scratch, S.d_out, S.stream));
-      HIPCHK(S, hipMemcpyAsync(fe, S.d_out, 2 * sizeof(double), hipMemcpyDeviceToHost, S.stream));
-      HIPCHK(S, hipStreamSynchronize(S.stream));
+      // every sum's kernels first, then one copy and one wait
+      double sums[2 + 4 * PIC_MAX_SPECIES] = {}, pm[4] = {0, 0, 0, 0};
+      const double* fe = sums;
+      int nsp = 0;
+      if (kind == PIC_DIAG_ENERGY)
+        HIPCHK(S, pic_launch_field_sums(S.d_inst + ii, g.ncell, (int)(S.steps & 1), S.d_scratch, S.d_out, S.stream));
       for (int s = 0; s < PIC_MAX_SPECIES; s++) {
         Species& sp = I.sp[s];
         if (!sp.used || sp.np == 0) continue;
         int k = store_desc_index(S, i, s);
-        double r[4];
-        HIPCHK(S, pic_launch_particle_sums(S.d_stores + k, (int)sp.np, sp.rqm, S.d_scratch, S.d_out, S.stream));
-        HIPCHK(S, hipMemcpyAsync(r, S.d_out, 4 * sizeof(double), hipMemcpyDeviceToHost, S.stream));
-        HIPCHK(S, hipStreamSynchronize(S.stream));
-        for (int q = 0; q < 4; q++) pm[q] += r[q];
+        HIPCHK(S, pic_launch_particle_sums(S.d_stores + k, (int)sp.np, sp.rqm, S.d_scratch, S.d_out + 2 + 4 * nsp,
+                                           S.stream));
+        nsp++;
       }
+      HIPCHK(S, hipMemcpyAsync(sums, S.d_out, (size_t)(2 + 4 * nsp) * sizeof(double), hipMemcpyDeviceToHost, S.stream));
+      HIPCHK(S, hipStreamSynchronize(S.stream));
+      for (int k = 0; k < nsp; k++)
+        for (int q = 0; q < 4; q++) pm[q] += sums[2 + 4 * k + q];
       double* o = (double*)out;
       // r-z: the field sums carry the ring volumes in units of dz dr^2, and a
       // particle's charge is w 2 pi dr^2 dz
@@ -1413,8 +1502,7 @@ pic_status sim_diag(Sim& S, int i, pic_diag_kind kind, void* out, size_t out_byt
         ((double*)out)[1] = std::sqrt(ss / (double)nc);
         return PIC_OK;
       }
-      HIPCHK(S, hipMemcpyAsync(out, src, nc * sizeof(double), hipMemcpyDeviceToHost, S.stream));
-      HIPCHK(S, hipStreamSynchronize(S.stream));
+      if ((st = export_copy(S, out, src, nc * sizeof(double))) != PIC_OK) return st;
       if (I.cfg.move_window) {
         WinCtl wc;
         if ((st = read_win(S, I, wc)) != PIC_OK) return st;
@@ -1448,7 +1536,7 @@ pic_status sim_diag(Sim& S, int i, pic_diag_kind kind, void* out, size_t out_byt
           // the ring column to the lab position (moving window), x2 from the
           // cell coordinate to the radius (r-z)
           int* dids = (int*)(scr + rb);
-          HIPCHK(S, pic_launch_export_state(S.d_stores + k, (int)sp.np, dbuf, dids, S.stream));
+          HIPCHK(S, pic_launch_export_state(S.d_stores + k, (int)sp.np, dbuf, dids, nullptr, nullptr, S.stream));
           std::vector<double> rows((size_t)sp.np * stride);
           std::vector<int> ids(sp.np);
           HIPCHK(S, hipMemcpyAsync(rows.data(), dbuf, rows.size() * sizeof(double), hipMemcpyDeviceToHost, S.stream));
@@ -1479,11 +1567,9 @@ pic_status sim_diag(Sim& S, int i, pic_diag_kind kind, void* out, size_t out_byt
             if (g.cyl) dst[1] = (r[1] - 0.5) * I.cfg.dx[1];  // r-z: the radius
           }
         } else {
-          HIPCHK(S, pic_launch_export_state(S.d_stores + k, (int)sp.np, dbuf, nullptr, S.stream));
-          HIPCHK(S, hipMemcpyAsync(o, dbuf, (size_t)sp.np * stride * sizeof(double), hipMemcpyDeviceToHost, S.stream));
-          HIPCHK(S, hipStreamSynchronize(S.stream));
-          for (int64_t p = 0; p < sp.np; p++)
-            for (int d = 0; d < g.dim; d++) o[p * stride + d] = I.cfg.xmin[d] + o[p * stride + d] * I.cfg.dx[d];
+          // scaled on the device to the caller's positions
+          HIPCHK(S, pic_launch_export_state(S.d_stores + k, (int)sp.np, dbuf, nullptr, I.cfg.xmin, I.cfg.dx, S.stream));
+          if ((st = export_copy(S, o, dbuf, (size_t)sp.np * stride * sizeof(double))) != PIC_OK) return st;
         }
         o += (size_t)sp.np * stride;
       }
@@ -1493,16 +1579,10 @@ pic_status sim_diag(Sim& S, int i, pic_diag_kind kind, void* out, size_t out_byt
     case PIC_DIAG_EXPORT_CURRENT: {
       size_t ncomp = kind == PIC_DIAG_EXPORT_FIELDS ? 6 : 3;
       if ((st = need(S, ncomp * nc * sizeof(double), out_bytes, written)) != PIC_OK) return st;
-      if ((st = diag_scratch(S, ncomp * nc * sizeof(double), &scr)) != PIC_OK) return st;
-      double* dbuf = (double*)scr;
-      HIPCHK(S, pic_launch_f32_to_f64(kind == PIC_DIAG_EXPORT_FIELDS ? I.F[S.steps & 1] : I.Jout, dbuf, ncomp * nc, S.stream));
-      HIPCHK(S, hipMemcpyAsync(out, dbuf, ncomp * nc * sizeof(double), hipMemcpyDeviceToHost, S.stream));
-      HIPCHK(S, hipStreamSynchronize(S.stream));
-      if (I.cfg.move_window) {
-        WinCtl wc;
-        if ((st = read_win(S, I, wc)) != PIC_OK) return st;
-        ring_rotate((double*)out, ncomp, g, wc.origin, true);
-      }
+      WinCtl wc;
+      if ((st = read_win(S, I, wc)) != PIC_OK) return st;
+      const float* src = kind == PIC_DIAG_EXPORT_FIELDS ? I.F[S.steps & 1] : I.Jout;
+      if ((st = export_planes(S, g, src, ncomp, wc.origin, (double*)out)) != PIC_OK) return st;
       if (g.cyl) {
         // r-z row 0: mirror images of row 1 for the whole-row components
         // (E_z +, E_theta -, B_r -; J_z +, J_theta -); the half-row
@@ -1536,8 +1616,7 @@ pic_status sim_diag(Sim& S, int i, pic_diag_kind kind, void* out, size_t out_byt
       o[3] = 0;
       for (Species& sp : I.sp) {
         if (!sp.used || !sp.ctl) continue;
-        StoreCtl c{};
-        HIPCHK(S, hipMemcpy(&c, sp.ctl, sizeof c, hipMemcpyDeviceToHost));
+        const StoreCtl& c = host_ctl(S, sp);
         o[1] += (double)sp.np;
         o[2] = std::max(o[2], (double)c.nsorts);
         o[3] = std::max(o[3], (double)c.nchecks);
@@ -1690,6 +1769,9 @@ pic_status sim_create(Sim& S, const pic_config* cfgs, int n, void* stream) {
   const char* env = getenv("PIC_NO_GRAPH");
   S.use_graph = !(env && env[0] == '1');
   S.inst.resize(n);
+  S.h_ctl.assign((size_t)n * PIC_MAX_SPECIES, StoreCtl{});
+  if (hipMalloc(&S.d_ctl, S.h_ctl.size() * sizeof(StoreCtl)) != hipSuccess)
+    return S.fail(PIC_E_NOMEM, "control word allocation failed");
   for (int i = 0; i < n; i++) {
     Instance& I = S.inst[i];
     I.cfg = cfgs[i];
@@ -1730,7 +1812,7 @@ pic_status sim_create(Sim& S, const pic_config* cfgs, int n, void* stream) {
     }
   }
   HIPCHK(S, hipMalloc(&S.d_scratch, (size_t)2 * 4 * pic_reduce_blocks() * sizeof(double)));
-  HIPCHK(S, hipMalloc(&S.d_out, 8 * sizeof(double)));
+  HIPCHK(S, hipMalloc(&S.d_out, (2 + 4 * PIC_MAX_SPECIES) * sizeof(double)));
   S.dirty = true;
   return PIC_OK;
 }
@@ -1776,6 +1858,7 @@ void sim_destroy(Sim& S) {
   if (S.d_scratch) (void)hipFree(S.d_scratch);
   if (S.d_out) (void)hipFree(S.d_out);
   if (S.d_diag) (void)hipFree(S.d_diag);
+  if (S.d_ctl) (void)hipFree(S.d_ctl);
   if (S.own_stream && S.stream) (void)hipStreamDestroy(S.stream);
 }
 
@@ -1958,6 +2041,7 @@ pic_status set_force(Sim& S, int v) {
   for (Instance& I : S.inst)
     for (Species& sp : I.sp)
       if (sp.used && sp.ctl) HIPCHK(S, hipMemcpy(&sp.ctl->force, &v, sizeof v, hipMemcpyHostToDevice));
+  S.ctl_current = false;
   return PIC_OK;
 }
 

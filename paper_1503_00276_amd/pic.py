@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from concurrent.futures import ThreadPoolExecutor
 from dataclasses import dataclass, field
 from typing import Optional, Sequence
 
@@ -268,6 +269,27 @@ def _stream_handle(stream) -> Optional[int]:
     return int(stream)
 
 
+def _split_rows(a: np.ndarray, d: int):
+    """(x, u, w) of exported rows, each contiguous.  Large exports are split by
+    several threads (numpy copies without the interpreter lock): the new
+    arrays' page faults cost more than the copy itself."""
+    n = len(a)
+    out = np.empty((n, d)), np.empty((n, 3)), np.empty(n)
+    parts = a[:, :d], a[:, d:d + 3], a[:, d + 3]
+
+    def fill(lo: int):
+        for o, p in zip(out, parts):
+            o[lo:lo + step] = p[lo:lo + step]
+
+    step = max(n, 1) if n < 1 << 18 else -(-n // 8)
+    if step >= n:
+        fill(0)
+    else:
+        with ThreadPoolExecutor(8) as ex:
+            list(ex.map(fill, range(0, n, step)))
+    return out
+
+
 class _Base:
     _h: C.c_void_p
 
@@ -357,11 +379,11 @@ class Pic(_Base):
         n = self.nparticles()
         d = self.cfg.ndim
         a = self.diag(PIC_DIAG_EXPORT_STATE, n * (d + 4)).reshape(n, d + 4)
-        return a[:, :d].copy(), a[:, d:d + 3].copy(), a[:, d + 3].copy()
+        return _split_rows(a, d)
 
     def fields(self):
         a = self.diag(PIC_DIAG_EXPORT_FIELDS, 6 * self.cfg.ncell).reshape(6, self.cfg.ncell)
-        return a[:3].copy(), a[3:].copy()
+        return a[:3], a[3:]
 
     def current(self):
         return self.diag(PIC_DIAG_EXPORT_CURRENT, 3 * self.cfg.ncell).reshape(3, self.cfg.ncell)
@@ -466,7 +488,7 @@ class PicBatch(_Base):
             n = self._np[inst]
         d = cfg.ndim
         a = self.diag(inst, PIC_DIAG_EXPORT_STATE, n * (d + 4)).reshape(n, d + 4)
-        return a[:, :d].copy(), a[:, d:d + 3].copy(), a[:, d + 3].copy()
+        return _split_rows(a, d)
 
     def profile(self, enable: int):
         self._check(self._L.pic_batch_profile(self._h, int(enable)))
@@ -491,7 +513,7 @@ class PicBatch(_Base):
     def fields(self, inst: int):
         nc = self.cfgs[inst].ncell
         a = self.diag(inst, PIC_DIAG_EXPORT_FIELDS, 6 * nc).reshape(6, nc)
-        return a[:3].copy(), a[3:].copy()
+        return a[:3], a[3:]
 
     def current(self, inst: int):
         nc = self.cfgs[inst].ncell
