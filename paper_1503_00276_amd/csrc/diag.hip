@@ -406,8 +406,10 @@ __global__ void __launch_bounds__(kBlock) export_state(const StoreDesc* __restri
     pic_unpack(g, cell, c);
     double* row = out + (size_t)(ids ? p : S.id[cur][p]) * stride;
     for (int d = 0; d < g.dim; d++) {
+#pragma clang fp contract(off)
       const double x = (double)c[d] + (double)S.eps[cur][d][p];
-      row[d] = ids ? x : __dadd_rn(sc.xmin[d], __dmul_rn(x, sc.dx[d]));
+      const double s = x * sc.dx[d];
+      row[d] = ids ? x : sc.xmin[d] + s;
     }
     row[g.dim + 0] = S.u[cur][0][p];
     row[g.dim + 1] = S.u[cur][1][p];
