@@ -63,6 +63,32 @@ hipError_t pic_launch_rebin(const StoreDesc* d_stores, int nstores, int max_item
                             int total_blocks, bool big, int inject_max, bool thermal, int parity,
                             hipStream_t st);
 
+// loading (load.hip): the new particles (FP64 rows in device memory) and the
+// ones already stored, sorted together into a buffer set of the store
+struct LoadStatus {
+  unsigned flags;            // non-finite: 1 positions, 2 momenta, 4 weights
+  unsigned long long first;  // 2 * the first new particle outside the window or (+ 1) beyond the wall
+  unsigned long long u2, w;  // bits of max |u|^2 of all and of max |w| of the new particles
+  int idmax;                 // largest id stored (-1: none)
+  int items;                 // work items planned
+};
+struct LoadArgs {
+  GridDesc g;
+  double xmin[3];
+  int shifts, origin;        // moving window
+  long long old, n, id0;     // particles stored, particles new, id of the first new one
+  const double *x, *u, *w;
+  const int *ocell, *oid;    // the stored ones
+  const float *oeps[3], *ou[3], *ow;
+  int* cells;                // [ntiles * tile volume] zeroed
+  int* tiles;                // [ntiles]
+  int *rank, *slot;          // [old + n]
+  LoadStatus* status;        // zeroed but first = ~0 and idmax = -1
+};
+hipError_t pic_launch_load_count(const LoadArgs& a, hipStream_t st);
+hipError_t pic_launch_load_place(const LoadArgs& a, const StoreDesc& s, int set, hipStream_t st);
+hipError_t pic_launch_neighbour_table(const GridDesc& g, int* ndst, hipStream_t st);
+
 // diagnostics (diag.hip)
 // adds a species' charge density; kstep: steps done since the last rebin
 // check, par: parity of the steps done

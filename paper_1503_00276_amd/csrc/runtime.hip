@@ -472,6 +472,9 @@ int default_chunk(const Sim& S, const pic_config& c, const GridDesc& g, int64_t 
   return all < (1 << 18) ? 256 : split(2048, 512, 2048);
 }
 
+// Bytes rounded up to a multiple of 256 (sub-buffers of an allocation).
+size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
 template <typename T>
 pic_status dalloc(Sim& S, std::vector<void*>& list, T** p, size_t n) {
   void* q = nullptr;
@@ -524,25 +527,33 @@ pic_status alloc_species(Sim& S, Instance& I, Species& sp, int64_t cap, int chun
   d.chunk = store_chunk(g, chunk);
   d.max_items = (int)std::min<int64_t>((int64_t)g.ntiles + cap / d.chunk + 1, 0x7fffffff);
   sp.max_items = d.max_items;
-  pic_status st;
-#define AL(ptr, n) \
-  if ((st = dalloc(S, sp.allocs, &(ptr), (size_t)(n))) != PIC_OK) return st
+  // one allocation for all arrays, each on a 256-byte boundary
+  std::vector<std::pair<void**, size_t>> parts;
+  auto al = [&](auto** p, size_t n) { parts.push_back({(void**)p, n * sizeof(**p)}); };
   for (int s = 0; s < 2; s++) {
-    AL(d.cell[s], cap);
-    for (int k = 0; k < g.dim; k++) AL(d.eps[s][k], cap);
-    for (int k = 0; k < 3; k++) AL(d.u[s][k], cap);
-    AL(d.w[s], cap);
-    AL(d.id[s], cap);
-    AL(d.toff[s], g.ntiles + 1);
-    AL(d.ioff[s], g.ntiles + 1);
-    AL(d.items[s], d.max_items);
+    al(&d.cell[s], cap);
+    for (int k = 0; k < g.dim; k++) al(&d.eps[s][k], cap);
+    for (int k = 0; k < 3; k++) al(&d.u[s][k], cap);
+    al(&d.w[s], cap);
+    al(&d.id[s], cap);
+    al(&d.toff[s], g.ntiles + 1);
+    al(&d.ioff[s], g.ntiles + 1);
+    al(&d.items[s], d.max_items);
   }
-  AL(d.pre, (size_t)d.max_items * PIC_NSLOT);
-  AL(d.dcount, g.ntiles);
+  al(&d.pre, (size_t)d.max_items * PIC_NSLOT);
+  al(&d.dcount, g.ntiles);
+  al(&d.bsum, (size_t)2 * ((g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES));
+  al(&d.bpre, (size_t)2 * ((g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES));
+  size_t bytes = 0;
+  for (auto& q : parts) bytes += align256(std::max<size_t>(q.second, 1));
+  char* slab = nullptr;
+  pic_status st;
+  if ((st = dalloc(S, sp.allocs, &slab, bytes)) != PIC_OK) return st;
+  for (auto& q : parts) {
+    *q.first = slab;
+    slab += align256(std::max<size_t>(q.second, 1));
+  }
   HIPCHK(S, hipMemset(d.dcount, 0, (size_t)g.ntiles * sizeof(int)));
-  AL(d.bsum, (size_t)2 * ((g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES));
-  AL(d.bpre, (size_t)2 * ((g.ntiles + PIC_REBIN_TILES - 1) / PIC_REBIN_TILES));
-#undef AL
   sp.ctl = S.d_ctl + ((&I - S.inst.data()) * PIC_MAX_SPECIES + (&sp - I.sp));
   d.ctl = sp.ctl;
   S.ctl_current = false;
@@ -1117,6 +1128,204 @@ pic_status first_load_tiles(Sim& S, Instance& I, int64_t n) {
   return build_tables(S, I);
 }
 
+pic_status diag_scratch(Sim& S, size_t bytes, char** p);
+
+// What a load has to allocate for a store of 'total' particles.
+int64_t wanted_capacity(const Instance& I, int species, int64_t total) {
+  if (!I.cfg.move_window || species != 0) return total;
+  // room for the window's plasma: a full window of injected lattice plus two
+  // columns in flight
+  int64_t ppc = 1;
+  for (int a = 0; a < I.g.dim; a++) ppc *= I.cfg.inject_ppc[a];
+  const int64_t col = ppc * (I.g.ncell / I.g.nx[0]);
+  return std::max<int64_t>(total, ppc * I.g.ncell) + 2 * col + 1024;
+}
+
+// A store's injection settings, its species' largest weight and the units of
+// the instance, once the new particles' largest weight is known.
+void settle_species(Instance& I, int species, double wm) {
+  Species& sp = I.sp[species];
+  I.wmax[species] = std::max(I.wmax[species], wm);
+  if (I.cfg.move_window && species == 0) {
+    for (int a = 0; a < 3; a++) sp.desc.inj_ppc[a] = a < I.g.dim ? I.cfg.inject_ppc[a] : 1;
+    sp.desc.inj_w = (float)I.cfg.inject_w;
+    sp.desc.inj_uth = I.cfg.inject_uth;
+    sp.desc.inj_seed = I.cfg.inject_seed;
+    // r-z: injected weights grow with the radius, up to (nr - 1/2) inject_w
+    const double wi = std::fabs(I.cfg.inject_w) * (I.g.cyl ? (double)I.g.nx[1] - 0.5 : 1.0);
+    I.wmax[0] = std::max(I.wmax[0], wi);
+  }
+  set_current_scale(I);
+}
+
+// Bound on |u| that also covers what a thermal window can inject (a Box-Muller
+// deviate from 53-bit uniforms is at most sqrt(2 * 53 ln 2) = 8.5717 per
+// component).
+float inject_umax(const Instance& I, int species) {
+  if (!I.cfg.move_window || species != 0 || !(I.cfg.inject_uth > 0.0)) return 0.0f;
+  return (float)(8.5718 * std::sqrt(3.0) * I.cfg.inject_uth * (1.0 + 1e-6));
+}
+
+// The load on the device.  *done stays false where the host's path has to take
+// the call: a state that is reported after the input's own checks, or too
+// little device memory for both the old and the new arrays.  The kernels run
+// on the null stream, as the copies of the host's path do, so they see what
+// was queued there (and on blocking streams) to produce the input.
+pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, const double* x, const double* u,
+                       const double* w, uint32_t flags, bool* done) {
+  Species& sp = I.sp[species];
+  const bool win = I.cfg.move_window != 0, rz = I.g.cyl != 0;
+  if (sim_sync(S) != PIC_OK) return PIC_OK;  // fresh particle counts (moving window)
+  const int64_t old = sp.np, total = old + n;
+  if ((I.cfg.capacity > 0 && total > I.cfg.capacity) || total > 0x7fffff00LL) return PIC_OK;
+  if (win && species != 0 && !I.sp[0].used) return PIC_OK;
+  if (first_load_tiles(S, I, n) != PIC_OK) return PIC_OK;
+  WinCtl wc;
+  pic_status st = read_win(S, I, wc);
+  if (st != PIC_OK) return st;
+  const GridDesc& g = I.g;
+  // input the kernels can read: memory of this device, aligned; else a copy
+  const double* in[3] = {x, u, w};
+  size_t in_bytes[3] = {(size_t)n * g.dim * 8, (size_t)n * 24, (size_t)n * 8}, stage = 0;
+  bool copy[3];
+  for (int k = 0; k < 3; k++) {
+    hipPointerAttribute_t pa;
+    copy[k] = true;
+    if ((flags & PIC_DEVICE_PTRS) && ((uintptr_t)in[k] & 7) == 0) {
+      if (hipPointerGetAttributes(&pa, in[k]) == hipSuccess)
+        copy[k] = pa.type != hipMemoryTypeDevice || pa.device != S.device;
+      else
+        (void)hipGetLastError();
+    }
+    if (copy[k]) stage += align256(in_bytes[k]);
+  }
+  const size_t nkey = (size_t)g.ntiles * g.tile[0] * g.tile[1] * g.tile[2];
+  const size_t bytes = 256 + align256(nkey * 4) + align256((size_t)g.ntiles * 4) + 2 * align256((size_t)total * 4) + stage;
+  // small loads use the diagnostics' scratch, large ones memory of their own
+  char* mem = nullptr;
+  void* own = nullptr;
+  if (bytes <= ((size_t)64 << 20)) {
+    if (diag_scratch(S, bytes, &mem) != PIC_OK) mem = nullptr;
+  } else if (hipMalloc(&own, bytes) == hipSuccess) {
+    mem = (char*)own;
+  }
+  if (!mem) {
+    (void)hipGetLastError();
+    return PIC_OK;
+  }
+  struct Free {
+    void* p;
+    ~Free() { (void)hipFree(p); }
+  } free_own{own};
+  *done = true;
+  LoadArgs A{};
+  A.g = g;
+  for (int d = 0; d < 3; d++) A.xmin[d] = I.cfg.xmin[d];
+  A.shifts = wc.shifts;
+  A.origin = wc.origin;
+  A.old = old;
+  A.n = n;
+  auto take = [&](size_t b) {
+    char* p = mem;
+    mem += align256(b);
+    return p;
+  };
+  A.status = (LoadStatus*)take(sizeof(LoadStatus));
+  static_assert(sizeof(LoadStatus) <= 256, "room for the status");
+  A.cells = (int*)take(nkey * 4);
+  A.tiles = (int*)take((size_t)g.ntiles * 4);
+  A.rank = (int*)take((size_t)total * 4);
+  A.slot = (int*)take((size_t)total * 4);
+  for (int k = 0; k < 3; k++)
+    if (copy[k]) {
+      char* p = take(in_bytes[k]);
+      HIPCHK(S, hipMemcpy(p, in[k], in_bytes[k], (flags & PIC_DEVICE_PTRS) ? hipMemcpyDefault : hipMemcpyHostToDevice));
+      in[k] = (const double*)p;
+    }
+  A.x = in[0];
+  A.u = in[1];
+  A.w = in[2];
+  StoreCtl c{};
+  int set = 0;
+  if (old > 0) {
+    c = host_ctl(S, sp);
+    const int cur = pic_cur(c);
+    const StoreDesc& d = sp.desc;
+    A.ocell = d.cell[cur];
+    A.oid = d.id[cur];
+    for (int k = 0; k < 3; k++) {
+      A.oeps[k] = d.eps[cur][k];
+      A.ou[k] = d.u[cur][k];
+    }
+    A.ow = d.w[cur];
+    set = 1 - cur;  // (the set read from stays as it is)
+  }
+  LoadStatus ls{};
+  ls.first = ~0ull;
+  ls.idmax = -1;
+  HIPCHK(S, hipMemcpy(A.status, &ls, sizeof ls, hipMemcpyHostToDevice));
+  HIPCHK(S, hipMemsetAsync(A.cells, 0, nkey * 4, nullptr));
+  HIPCHK(S, pic_launch_load_count(A, nullptr));
+  HIPCHK(S, hipMemcpy(&ls, A.status, sizeof ls, hipMemcpyDeviceToHost));
+  if (ls.flags & 1) return S.fail(PIC_E_RANGE, "non-finite position");
+  if (ls.flags & 2) return S.fail(PIC_E_RANGE, "non-finite momentum");
+  if (ls.flags & 4) return S.fail(PIC_E_RANGE, "non-finite weight");
+  A.id0 = win ? wc.next_id : (rz ? (int64_t)ls.idmax + 1 : old);
+  if (rz && A.id0 + n > 0x7fffff00LL) return S.fail(PIC_E_NOMEM, "particle ids exhausted");
+  if (ls.first != ~0ull)
+    return (ls.first & 1) ? S.fail(PIC_E_RANGE, "particle radius outside [0, (nr - 1/2) dr)")
+                          : S.fail(PIC_E_RANGE, "particle outside the moving window");
+  double u2, wm;
+  memcpy(&u2, &ls.u2, 8);
+  memcpy(&wm, &ls.w, 8);
+  const int64_t want = wanted_capacity(I, species, total);
+  Species keep;  // the arrays the load reads from, until it is done
+  if (!sp.used || want > sp.cap) {
+    keep = sp;
+    sp.allocs.clear();
+    const int64_t cap = I.cfg.capacity > 0 ? std::max<int64_t>(I.cfg.capacity, want) : want;
+    const int chunk = I.cfg.chunk > 0 ? I.cfg.chunk : default_chunk(S, I.cfg, I.g, want);
+    if (alloc_species(S, I, sp, std::max<int64_t>(cap, 1), chunk) != PIC_OK) {
+      (void)hipGetLastError();
+      for (void* p : sp.allocs) (void)hipFree(p);
+      sp = keep;
+      if (sp.ctl) HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
+      *done = false;
+      return PIC_OK;
+    }
+    sp.used = true;
+    sp.rqm = rqm;
+    sp.desc.qm = (float)(1.0 / rqm);
+    set = 0;
+    c = StoreCtl{};
+  }
+  settle_species(I, species, wm);
+  hipError_t e = pic_launch_load_place(A, sp.desc, set, nullptr);
+  if (e == hipSuccess) e = hipMemcpy(&ls, A.status, sizeof ls, hipMemcpyDeviceToHost);
+  for (void* p : keep.allocs) (void)hipFree(p);
+  HIPCHK(S, e);
+  if (ls.items > sp.max_items) return S.fail(PIC_E_NOMEM, "work item list overflow");
+  c.cur = set;
+  c.pending = c.flag = c.active = c.bad = 0;
+  c.n_items[set] = ls.items;
+  c.n_items[1 - set] = 0;
+  c.sorted = 1;  // binned exactly: every particle in its own tile
+  // the one-phase kernels' bound on |u| covers every particle of the store
+  c.umax = std::max(c.umax, std::nextafter((float)(std::sqrt(u2) * (1.0 + 1e-6)), INFINITY));
+  c.umax = std::max(c.umax, inject_umax(I, species));
+  if (win || rz) c.np = (int)total;
+  HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
+  S.ctl_current = false;
+  sp.np = total;
+  sp.desc.np = (int)total;
+  S.dirty = true;
+  if (win) {
+    wc.next_id += n;
+    HIPCHK(S, hipMemcpy(I.win + (S.steps & 1), &wc, sizeof wc, hipMemcpyHostToDevice));
+  }
+  return PIC_OK;
+}
+
 pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, const double* x,
                     const double* u, const double* w, uint32_t flags) {
   if (inst < 0 || inst >= (int)S.inst.size()) return S.fail(PIC_E_INVALID, "instance %d out of range", inst);
@@ -1129,8 +1338,13 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
   HIPCHK(S, hipStreamSynchronize(S.stream));
   if (sp.used && sp.rqm != rqm) return S.fail(PIC_E_INVALID, "rqm differs from the species' first load");
   const int dim = I.g.dim;
-  std::vector<double> hx, hu, hw;
   pic_status st;
+  if (n > 0) {
+    bool done = false;
+    st = load_device(S, I, species, rqm, n, x, u, w, flags, &done);
+    if (done || st != PIC_OK) return st;
+  }
+  std::vector<double> hx, hu, hw;
   if ((st = copy_in(S, hx, x, (size_t)n * dim, flags)) != PIC_OK) return st;
   if ((st = copy_in(S, hu, u, (size_t)n * 3, flags)) != PIC_OK) return st;
   if ((st = copy_in(S, hw, w, (size_t)n, flags)) != PIC_OK) return st;
@@ -1200,18 +1414,9 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
     for (int k = 0; k < 3; k++) h.u[k][old + p] = (float)hu[p * 3 + k];
     h.w[old + p] = (float)hw[p];
   }
-  double wm = I.wmax[species];
+  double wm = 0.0;
   for (double v : hw) wm = std::max(wm, std::fabs(v));
-  I.wmax[species] = wm;
-  int64_t want = total;
-  if (win && species == 0) {
-    // room for the window's plasma: a full window of injected lattice plus
-    // two columns in flight
-    int64_t ppc = 1;
-    for (int a = 0; a < dim; a++) ppc *= I.cfg.inject_ppc[a];
-    int64_t col = ppc * (I.g.ncell / I.g.nx[0]);
-    want = std::max<int64_t>(total, ppc * I.g.ncell) + 2 * col + 1024;
-  }
+  const int64_t want = wanted_capacity(I, species, total);
   if (!sp.used || want > sp.cap) {
     int64_t cap = I.cfg.capacity > 0 ? std::max<int64_t>(I.cfg.capacity, want) : want;
     int chunk = I.cfg.chunk > 0 ? I.cfg.chunk : default_chunk(S, I.cfg, I.g, want);
@@ -1220,16 +1425,7 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
     sp.rqm = rqm;
     sp.desc.qm = (float)(1.0 / rqm);
   }
-  if (win && species == 0) {
-    for (int a = 0; a < 3; a++) sp.desc.inj_ppc[a] = a < dim ? I.cfg.inject_ppc[a] : 1;
-    sp.desc.inj_w = (float)I.cfg.inject_w;
-    sp.desc.inj_uth = I.cfg.inject_uth;
-    sp.desc.inj_seed = I.cfg.inject_seed;
-    // r-z: injected weights grow with the radius, up to (nr - 1/2) inject_w
-    const double wi = std::fabs(I.cfg.inject_w) * (rz ? (double)I.g.nx[1] - 0.5 : 1.0);
-    I.wmax[0] = std::max(I.wmax[0], wi);
-  }
-  set_current_scale(I);
+  settle_species(I, species, wm);
   if (win) {
     wc.next_id += n;
     HIPCHK(S, hipMemcpy(I.win + (S.steps & 1), &wc, sizeof wc, hipMemcpyHostToDevice));
@@ -1239,11 +1435,7 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
     StoreCtl c{};
     HIPCHK(S, hipMemcpy(&c, sp.ctl, sizeof c, hipMemcpyDeviceToHost));
     c.np = (int)sp.np;
-    // the bound on |u| also covers what a thermal window can inject (a
-    // Box-Muller deviate from 53-bit uniforms is at most sqrt(2 * 53 ln 2) =
-    // 8.5717 per component)
-    if (win && species == 0 && I.cfg.inject_uth > 0.0)
-      c.umax = std::max(c.umax, (float)(8.5718 * std::sqrt(3.0) * I.cfg.inject_uth * (1.0 + 1e-6)));
+    c.umax = std::max(c.umax, inject_umax(I, species));
     HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
     S.ctl_current = false;
   }
@@ -1334,9 +1526,6 @@ pic_status diag_scratch(Sim& S, size_t bytes, char** p) {
   *p = (char*)S.d_diag;
   return PIC_OK;
 }
-
-// Bytes rounded up to a multiple of 256 (sub-buffers of the scratch).
-static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 pic_status need(Sim& S, size_t want, size_t out_bytes, size_t* written) {
   if (written) *written = want;
@@ -1707,22 +1896,12 @@ pic_status sim_diag_noalloc(Sim& S, int i, pic_diag_kind kind, void* out, size_t
 // periodic in tiles.
 pic_status build_tables(Sim& S, Instance& I) {
   const GridDesc& g = I.g;
-  std::vector<int> nd((size_t)g.ntiles * PIC_NSLOT);
-  for (int t = 0; t < g.ntiles; t++) {
-    int tc[3];
-    pic_tile_coords(g, t, tc);
-    for (int sl = 0; sl < PIC_NSLOT; sl++) {
-      int dd[3] = {sl % 3 - 1, (sl / 3) % 3 - 1, sl / 9 - 1};
-      int b[3];
-      for (int d = 0; d < 3; d++) b[d] = pic_wrap(tc[d] + dd[d], g.ntile[d]);
-      nd[(size_t)t * PIC_NSLOT + sl] = pic_tile_index(g, b[0], b[1], b[2]);
-    }
-  }
   if (I.ndst) (void)hipFree(I.ndst);
   I.ndst = nullptr;
-  if (hipMalloc(&I.ndst, nd.size() * sizeof(int)) != hipSuccess)
+  if (hipMalloc(&I.ndst, (size_t)g.ntiles * PIC_NSLOT * sizeof(int)) != hipSuccess)
     return S.fail(PIC_E_NOMEM, "tile table allocation failed");
-  HIPCHK(S, hipMemcpy(I.ndst, nd.data(), nd.size() * sizeof(int), hipMemcpyHostToDevice));
+  HIPCHK(S, pic_launch_neighbour_table(g, I.ndst, nullptr));
+  HIPCHK(S, hipStreamSynchronize(nullptr));
   return PIC_OK;
 }
 
