@@ -39,6 +39,13 @@ hipError_t pic_launch_gpd(int dim, int order, int mode, const StoreDesc* d_store
 int pic_yee_tiles(int dim, const int nx[3], bool window);
 // whether a periodic 3D box takes the field step that marches along z
 bool pic_yee_marches(const int nx[3]);
+// current smoothing: Cartesian instances whose passes fit LDS tiles take them
+// all in one launch (max_level: most passes of such an instance per axis); the
+// others (r-z, many passes in 3D) one launch per pass and axis
+bool pic_smooth_in_tiles(int dim, const int level[3]);
+int pic_smooth_tiles(int dim, const int nx[3]);
+hipError_t pic_launch_smooth_tiles(const InstDesc* d_inst, int ninst, int dim, int max_tiles, const int max_level[3],
+                                   int parity, hipStream_t st);
 hipError_t pic_launch_smooth_pass(const InstDesc* d_inst, int ninst, int max_ncell, int axis, int lev,
                                   int parity, hipStream_t st);
 // cart / cyl: the group holds Cartesian / r-z instances (each kernel skips the

@@ -67,7 +67,9 @@ struct Group {
   int dim, order, first, count, max_ncell, max_items, max_tiles, max_blocks;
   size_t lds;
   bool fixed64;
-  int sm_max[3];  // most smoothing passes of any instance, per axis
+  int sm_max[3];  // most smoothing passes of any instance launched pass by pass, per axis
+  int sm_tiles_max[3] = {0, 0, 0};  // the same of the instances smoothed in tiles
+  int sm_tiles = 0;                 // most tiles of one of those (0: none)
   int inject_max; // moving window: most particles a store injects per shift
   bool window;    // some instance has a moving window
   bool thermal = false;  // stores: some moving window injects thermal momenta
@@ -652,7 +654,6 @@ pic_status refresh_descriptors(Sim& S) {
         id.sm_level[a] = lv;
         id.sm_first[a] = npass;
         npass += lv;
-        gr.sm_max[a] = std::max(gr.sm_max[a], lv);
         for (int p = 0; p < lv; p++) {
           const double* wt = I.cfg.smooth_weights[a][p];
           const double s = wt[0] + wt[1] + wt[2];
@@ -660,6 +661,14 @@ pic_status refresh_descriptors(Sim& S) {
         }
       }
       id.sm_npass = npass;
+      if (npass > 0) {
+        const bool tiles = !I.g.cyl && pic_smooth_in_tiles(I.g.dim, id.sm_level);
+        for (int a = 0; a < 3; a++) {
+          int& most = tiles ? gr.sm_tiles_max[a] : gr.sm_max[a];
+          most = std::max(most, id.sm_level[a]);
+        }
+        if (tiles) gr.sm_tiles = std::max(gr.sm_tiles, pic_smooth_tiles(I.g.dim, I.g.nx));
+      }
       id.Jsm[0] = I.Jsm[0];
       id.Jsm[1] = I.Jsm[1];
       id.win = I.win;
@@ -800,6 +809,10 @@ pic_status launch_steps(Sim& S, int64_t first, int nsteps, bool end_with_check, 
     }
     if (p0) S.ev_pending[0].push_back({p0, p1});
     hipEvent_t e0 = prof_begin(S);
+    for (const Group& gr : S.igroups)
+      if (gr.sm_tiles > 0)
+        HIPCHK(S, pic_launch_smooth_tiles(S.d_inst + gr.first, gr.count, gr.dim, gr.sm_tiles, gr.sm_tiles_max, par,
+                                          S.stream));
     for (const Group& gr : S.igroups)
       for (int a = 0; a < gr.dim; a++)
         for (int lev = 0; lev < gr.sm_max[a]; lev++)
