@@ -204,16 +204,17 @@ bool two_phase2(const pic_config& c) {
 //     1, 2, 4, 8 per cell 295 / 219 / 175, 313 / 242 / 223, 363 / 319 / 350,
 //     522 / 572 / 572; cubic 375 / 267 / 249, 405 / 319 / 330, 483 / 457 / 548,
 //     733 / 837 / 958; linear 222 / 157 / 131 ... 375 / 389 / 387.
-//   2D, two-phase kernel: 1,024 tiles (one wave of workgroups), from 64 to 512
+//   2D, two-phase kernel: 1,024 tiles (one wave of workgroups), from 64 to 256
 //     cells: 64x64 8x8 16.7 us, 16x16 17.9; 512x256 at 4 per cell 16x8 32, 16x16
-//     38; 1024x512 at 8 per cell 16x8 155, 16x16 144, 32x16 140.
+//     38; 1024x512 at 8 per cell 16x8 155, 16x16 144, 32x16 140; a batch of 24
+//     boxes, 7.7 M particles, 16x8 254, 16x16 251, 32x8 249, 32x16 270.
 //   2D, one-phase kernel: 512 tiles, from 128 to 256 cells.
 //   3D, one-phase kernel: 512 cells.
 // total: cells of all instances, which fill the chip together.
 double default_tile_cells(const GridDesc& g, int64_t total, double ppc) {
   if (pic_gpd_split(g)) return ppc > 0.0 ? std::min(256.0, std::max(64.0, 512.0 / ppc)) : 64.0;
   if (g.dim == 3) return 512.0;
-  if (pic_gpd_two_phase2(g)) return std::min(512.0, std::max(64.0, (double)total / 1024.0));
+  if (pic_gpd_two_phase2(g)) return std::min(256.0, std::max(64.0, (double)total / 1024.0));
   return std::min(256.0, std::max(128.0, (double)total / 512.0));
 }
 
