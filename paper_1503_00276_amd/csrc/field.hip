@@ -46,40 +46,6 @@ __device__ __forceinline__ int wrap1(int v, int n) {
 
 // WIN: compiled with the moving-window terms (launched for groups that hold a
 // moving window).
-// The fixed point of this step's current, per store whose particles take
-// the one-phase fused kernel with FP32 accumulation (Cartesian).  A
-// contribution of particle p to one node is at most |w_p| |v_p| (the charge
-// fraction that crosses a face in a step is at most the displacement in
-// cells; the transverse weight is at most one), and the Boris step changes
-// |u| by at most |q/m| dt |E| at the particle, where a gathered E_c is a
-// convex combination of node values: |E| <= sqrt(3) max|E_c| + |E_0|.  The
-// store keeps umax, a bound on |u| at the start of the step, and the
-// instance a running bound on |E_c| (set at a field load, raised by the Yee
-// step), so V = max|w| min(1, umax + kick) bounds every contribution of the
-// step, and the unit 2^-e with 2^e V 1.0001 < 2^31 keeps each inside an
-// int32: it follows the plasma's speed rather than c.  umax then advances
-// by the kick for the next step.  The int64 mode keeps the instance's unit
-// (its sums are exact in one unit), and so do r-z (whose field step keeps no
-// bound) and the two-phase 3D kernel (which takes a unit per work item).
-__global__ void current_units(StoreDesc* __restrict__ stores, int nstores) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nstores) return;
-  StoreDesc& D = stores[k];
-  const GridDesc& g = D.g;
-  if (g.acc_mode == 2 || g.cyl || pic_gpd_split(g)) return;
-  const float em = *(const gfloat*)D.emax;
-  const float e0n = sqrtf(g.e0[0] * g.e0[0] + g.e0[1] * g.e0[1] + g.e0[2] * g.e0[2]);
-  const float kick = fabsf(D.qm) * g.dt * (1.7320509f * em + e0n) * 1.0001f;
-  const float um = (D.ctl->umax + kick) * 1.000001f;
-  D.ctl->umax = um;
-  const float V = D.wmax * fminf(1.0f, um * 1.0001f);
-  int ex = 0;
-  (void)frexpf(V * 1.0001f, &ex);
-  const int e = V > 0.0f ? min(100, max(-100, 31 - ex)) : 100;
-  D.g.jscale = ldexpf(1.0f, e);
-  D.g.jinv = ldexpf(1.0f, -e);
-}
-
 // Which field step a periodic 3D box takes: runs of planes along z
 // (yee_march3) or 16x4x4 tiles (yee_step).
 // A long run re-reads little (two planes of E and one of B at its start), but
@@ -1124,11 +1090,6 @@ int pic_yee_tiles(int dim, const int nx[3], bool window) {
 }
 
 bool pic_yee_marches(const int nx[3]) { return march_run(nx) > 0; }
-
-hipError_t pic_launch_current_units(StoreDesc* d_stores, int nstores, hipStream_t st) {
-  hipLaunchKernelGGL(current_units, dim3((nstores + 63) / 64), dim3(64), 0, st, d_stores, nstores);
-  return hipGetLastError();
-}
 
 hipError_t pic_launch_yee_step(const InstDesc* d_inst, int ninst, int max_tiles, int dim, bool cart, bool cyl,
                                bool window, bool march, bool tiles, int parity, const StoreDesc* d_plan, int nplan,

@@ -254,6 +254,42 @@ __device__ __forceinline__ void lds_add_any(unsigned* p, float v) {
   __hip_atomic_fetch_add(p, (unsigned)cvt_rpi(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// The fixed point of a step's current, per store whose particles take the
+// one-phase kernel with FP32 accumulation (Cartesian).  A contribution of
+// particle p to one node is at most |w_p| |v_p| (the charge fraction that
+// crosses a face in a step is at most the displacement in cells; the
+// transverse weight is at most one), and the Boris step changes |u| by at most
+// |q/m| dt |E| at the particle, where a gathered E_c is a convex combination
+// of node values: |E| <= sqrt(3) max|E_c| + |E_0|.  The store keeps umax, a
+// bound on |u| at the start of the step, and the instance a running bound on
+// |E_c| (set at a field load, raised by the Yee step), so V = max|w| min(1,
+// umax + kick) bounds every contribution of the step, and the unit 2^-e with
+// 2^e V 1.0001 < 2^31 keeps each inside an int32: it follows the plasma's
+// speed rather than c.  The raised bound is the next step's umax.  The int64
+// mode keeps the instance's unit (its sums are exact in one unit), and so does
+// r-z (whose field step keeps no bound).
+// Every workgroup works the units out at its start, beside the item counts
+// (one memory latency for both), and the first one writes the bounds into the
+// entries of the other step parity.  A kernel of its own for this cost 4.3 to
+// 4.7 us a step; here it leaves the particle kernels as they were (order 1,
+// TRISTAN, 250x170 cells at 12: 19.1 and 19.2 us; order 2, moving window,
+// 768x192 cells at 8: 57.9 and 58.0).
+// The item gets the exponent only: the bound worked out per item took 2 vector
+// registers, and with them the order-1 kernel's sixth wave (22.0 us).
+__device__ __forceinline__ float step_umax(const StoreDesc& S, float umax, float emax) {
+  const GridDesc& g = S.g;
+  const float e0n = sqrtf(g.e0[0] * g.e0[0] + g.e0[1] * g.e0[1] + g.e0[2] * g.e0[2]);
+  const float kick = fabsf(S.qm) * g.dt * (1.7320509f * emax + e0n) * 1.0001f;
+  return (umax + kick) * 1.000001f;
+}
+
+__device__ __forceinline__ int step_exponent(const StoreDesc& S, float um) {
+  const float V = S.wmax * fminf(1.0f, um * 1.0001f);
+  int ex = 0;
+  (void)frexpf(V * 1.0001f, &ex);
+  return V > 0.0f ? min(100, max(-100, 31 - ex)) : 100;
+}
+
 // Fixed point of one work item's 32-bit current tile, whose node sums are at
 // most b in magnitude: Q = 2^e with Q b (1 + 2^-12) < 2^31.  b comes from FP32
 // sums, and FP32 rounding lets a contribution exceed its share of b by a few
@@ -520,8 +556,8 @@ __device__ __forceinline__ void dep3_comp(Acc* J, int cb, const int st[3], const
 // sort cycle).  count: the step's rebin check follows, so the particles are
 // counted by destination tile (the other steps of a cycle skip that).
 template <int DIM, int ORDER, int MODE>
-__device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii, int jp, int kstep, bool count, float* smem,
-                             int* scnt) {
+__device__ void process_item(const StoreDesc& S, int cur, int unit, const Item it, int ii, int jp, int kstep, bool count,
+                             float* smem, int* scnt) {
   constexpr int NG = ORDER + 1;  // gather taps per axis
   constexpr int W = ORDER + 2;   // deposit window per axis
   constexpr bool WIN = MODE == 1 || MODE == 3;
@@ -651,9 +687,9 @@ __device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii,
   for (int idx = tid; idx < 3 * jn; idx += blockDim.x) sJ[idx] = 0ull;
   if (tid < PIC_NSLOT) scnt[tid] = 0;
   __syncthreads();
-  // the instance's fixed point (see the host's current scale); the two-phase
-  // 3D kernel below chooses one per work item instead
-  const float Qi = g.jscale;
+  // the store's fixed point of this step, or the instance's (see the host's
+  // current scale); the two-phase kernels below choose one per work item instead
+  const float Qi = MODE <= 1 ? __int_as_float(unit << 23) : g.jscale;
 
   const float h = 0.5f * S.qm * g.dt;
   bool strayed = false, bad = false, died = false;
@@ -1099,7 +1135,7 @@ __device__ void process_item(const StoreDesc& S, int cur, const Item it, int ii,
 
   // 4. fold the LDS current into the global current (periodic wrap): FP32
   // atomics of the sums times the unit, or int64 atomics of the sums
-  const float qinv = g.jinv;
+  const float qinv = MODE <= 1 ? __int_as_float((254 - unit) << 23) : g.jinv;
   BoxWalk bj(tid, blockDim.x, JR);
   for (int idx = tid; idx < jn; idx += blockDim.x, bj.advance(JR)) {
     int gx = wrap_fast(org[0] - jlo[0] + bj.x, g.nx[0]);
@@ -2043,11 +2079,25 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
   __shared__ int s_cur[kMaxGroup];
   __shared__ int s_cnt[PIC_NSLOT];
   __shared__ float s_red[3 * (kBlock / 64)];
+  // per store its buffer set (bit 0) and, for the one-phase Cartesian kernels,
+  // the biased exponent of its unit of this step (above it); the first wave
+  // counts the items, the others take the units, so their loads overlap
+  if (MODE <= 1 && threadIdx.x >= 64)
+    for (int s = threadIdx.x - 64; s < nstores; s += kBlock - 64) {
+      const StoreDesc& S = stores[s];
+      int e = (__float_as_int(S.g.jscale) >> 23) & 255;
+      if (S.g.acc_mode != 2) {
+        const float um = step_umax(S, S.ctl->umax[jp], *(const gfloat*)S.emax);
+        e = 127 + step_exponent(S, um);
+        if (blockIdx.x == 0) S.ctl->umax[1 - jp] = um;  // (nothing else of this step reads this entry)
+      }
+      s_cur[s] = pic_cur(*S.ctl) | e << 1;
+    }
   if (threadIdx.x == 0) {
     int acc = 0;
     for (int s = 0; s < nstores; s++) {
-      int cur = pic_cur(*stores[s].ctl);
-      s_cur[s] = cur;
+      const int cur = pic_cur(*stores[s].ctl);
+      if (MODE > 1) s_cur[s] = cur;
       s_pref[s] = acc;
       acc += stores[s].ctl->n_items[cur];
     }
@@ -2076,7 +2126,7 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
     // into scalar registers, so the descriptor's fields load as scalars
     s = __builtin_amdgcn_readfirstlane(s);
     const StoreDesc& S = stores[s];
-    const int cur = __builtin_amdgcn_readfirstlane(s_cur[s]);
+    const int unit = __builtin_amdgcn_readfirstlane(s_cur[s]) >> 1, cur = __builtin_amdgcn_readfirstlane(s_cur[s]) & 1;
     const int ii = __builtin_amdgcn_readfirstlane(gi - s_pref[s]);
     Item it = S.items[cur][ii];
     it.tile = __builtin_amdgcn_readfirstlane(it.tile);
@@ -2088,7 +2138,7 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
       process_item3<ORDER, MODE == 5, typename std::conditional<MODE == 4, acc_t, unsigned>::type>(
           S, cur, it, ii, jp, kstep, count, smem, s_cnt, s_red);
     else
-      process_item<DIM, ORDER, MODE>(S, cur, it, ii, jp, kstep, count, smem, s_cnt);
+      process_item<DIM, ORDER, MODE>(S, cur, unit, it, ii, jp, kstep, count, smem, s_cnt);
   }
   (void)lo;
 }

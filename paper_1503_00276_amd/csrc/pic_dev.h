@@ -67,9 +67,10 @@ struct StoreCtl {
                     // every k-th check (nchecks % k == 0), flagged or not
   int np;           // particles in the current set after the last rebin (moving window)
   int sorted;       // 1: every particle sits in its own tile (loaded, or re-sorted at the last check)
-  float umax;       // bound on |u| of the store's particles at the start of the step: set at
-                    // a load (with the largest thermal momentum a moving window can inject),
-                    // raised at every step by the largest kick it can give (see gpd_body)
+  float umax[2];    // bound on |u| of the store's particles at the start of a step, by the
+                    // step's parity: set at a load (with the largest thermal momentum a
+                    // moving window can inject), raised at every step by the largest kick it
+                    // can give (step_umax in the fused kernel)
 };
 
 __host__ __device__ inline int pic_cur(const StoreCtl& c) { return c.cur ^ c.pending; }

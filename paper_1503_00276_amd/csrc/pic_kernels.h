@@ -54,9 +54,6 @@ hipError_t pic_launch_smooth_pass(const InstDesc* d_inst, int ninst, int max_nce
 // boxes that march along z / that take the 3D tiles.  The launch also advances
 // the moving windows and, with nplan > 0, plans the rebin check of the nplan
 // stores at d_plan (those of at most pic_plan_tiles() tiles).
-// Per store: this step's fixed point of the one-phase kernels' FP32 current
-// (from the store's bound on |u| and the instance's bound on |E_c|).
-hipError_t pic_launch_current_units(StoreDesc* d_stores, int nstores, hipStream_t st);
 hipError_t pic_launch_yee_step(const InstDesc* d_inst, int ninst, int max_tiles, int dim, bool cart, bool cyl,
                                bool window, bool march, bool tiles, int parity, const StoreDesc* d_plan, int nplan,
                                hipStream_t st);

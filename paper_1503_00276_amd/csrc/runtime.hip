@@ -74,7 +74,6 @@ struct Group {
   bool window;    // some instance has a moving window
   bool thermal = false;  // stores: some moving window injects thermal momenta
   bool big = false;    // stores: some store has more tiles than the field step's launch plans
-  bool units = false;  // stores: some store takes a per-step current unit (current_units)
   int mode = 0;   // stores: boundary logic of the fused kernel (0 periodic, 1 moving window, 2 r-z)
   int resident = 1;  // stores: fused-kernel workgroups resident per CU (the grid is one full wave of them)
   // stores, per step of a sort cycle: the LDS that step stages (its halo
@@ -610,8 +609,6 @@ pic_status refresh_descriptors(Sim& S) {
           if (I.g.window) gr.window = true;
           if (I.g.ntiles > pic_plan_tiles()) gr.big = true;
           if (sp.desc.inj_uth > 0.0) gr.thermal = true;
-          if (I.g.acc_mode != PIC_ACC_FIXED64 && !I.g.cyl && !pic_gpd_split(I.g) && !pic_gpd_two_phase2(I.g))
-            gr.units = true;
           gr.inject_max = std::max(gr.inject_max, sp.desc.inj_ppc[0] * sp.desc.inj_ppc[1] * sp.desc.inj_ppc[2] *
                                                       (I.g.ncell / I.g.nx[0]));
         }
@@ -793,8 +790,6 @@ pic_status launch_steps(Sim& S, int64_t first, int nsteps, bool end_with_check, 
       p1 = take_event(S);
       if (!p0 || !p1) p0 = p1 = nullptr;
     }
-    for (const Group& gr : S.sgroups)
-      if (gr.units) HIPCHK(S, pic_launch_current_units(S.d_stores + gr.first, gr.count, S.stream));
     for (size_t q = 0; q < S.sgroups.size(); q++) {
       const Group& gr = S.sgroups[q];
       // one full wave of resident workgroups: a partial second wave would
@@ -903,6 +898,11 @@ pic_status read_win(Sim& S, const Instance& I, WinCtl& w) {
 
 // Host copy of a store's control words (after sim_sync).
 const StoreCtl& host_ctl(const Sim& S, const Species& sp) { return S.h_ctl[sp.ctl - S.d_ctl]; }
+
+// Raise a store's bound on |u| to at least um, for either parity of the next step.
+void raise_umax(StoreCtl& c, float um) {
+  c.umax[0] = c.umax[1] = std::max(um, std::max(c.umax[0], c.umax[1]));
+}
 
 // Wait for the stream and bring the host's control words up to date: one copy
 // and one wait for all stores.  (One blocking copy per store made every
@@ -1079,7 +1079,7 @@ pic_status upload_bins(Sim& S, Species& sp, const Binned& B) {
   for (size_t q = 0; q < n; q++)
     um = std::max(um, std::sqrt((double)o.u[0][q] * o.u[0][q] + (double)o.u[1][q] * o.u[1][q] +
                                 (double)o.u[2][q] * o.u[2][q]));
-  c.umax = std::max(c.umax, std::nextafter((float)(um * (1.0 + 1e-6)), INFINITY));
+  raise_umax(c, std::nextafter((float)(um * (1.0 + 1e-6)), INFINITY));
   HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
   S.ctl_current = false;
   sp.np = (int64_t)n;
@@ -1325,8 +1325,8 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
   c.n_items[1 - set] = 0;
   c.sorted = 1;  // binned exactly: every particle in its own tile
   // the one-phase kernels' bound on |u| covers every particle of the store
-  c.umax = std::max(c.umax, std::nextafter((float)(std::sqrt(u2) * (1.0 + 1e-6)), INFINITY));
-  c.umax = std::max(c.umax, inject_umax(I, species));
+  raise_umax(c, std::nextafter((float)(std::sqrt(u2) * (1.0 + 1e-6)), INFINITY));
+  raise_umax(c, inject_umax(I, species));
   if (win || rz) c.np = (int)total;
   HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
   S.ctl_current = false;
@@ -1449,7 +1449,7 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
     StoreCtl c{};
     HIPCHK(S, hipMemcpy(&c, sp.ctl, sizeof c, hipMemcpyDeviceToHost));
     c.np = (int)sp.np;
-    c.umax = std::max(c.umax, inject_umax(I, species));
+    raise_umax(c, inject_umax(I, species));
     HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
     S.ctl_current = false;
   }
