@@ -37,6 +37,14 @@ template <> struct YeeTile<3> { static constexpr int X = 16, Y = 4, Z = 4; };
 // The fields are double-buffered: the step reads E^n, B^n from set par and
 // writes E^{n+1}, B^{n+1} to the other set, so a tile never reads a halo
 // node that a neighbouring workgroup has already advanced.
+// A small box has about one tile per CU, and its time is the tile's chain of
+// memory latencies, barriers and loop rounds.  So each part takes its region in
+// flat order (2 or 3 rounds of the workgroup; rows of the tile's width took 4
+// in 2D and 8 in 3D) with the LDS strides of a whole tile (no division by a
+// runtime extent), and the current is loaded with the staging instead of after
+// two barriers.  Per step, with rows and late loads and so: 64x64 6.4 -> 4.6 us,
+// 300x200 7.0 -> 5.7, 1024x256 9.8 -> 9.1, 45x37x53 12.2 -> 8.6, 128x64x64
+// 28.1 -> 25.2, r-z 384x96 10.3 -> 7.7.
 // Periodic wrap for an index at most one period out of range.
 __device__ __forceinline__ int wrap1(int v, int n) {
   v = v < 0 ? v + n : v;
@@ -53,9 +61,9 @@ __device__ __forceinline__ int wrap1(int v, int n) {
 // each, so the run shortens until the box makes 1,024 workgroups (four per
 // CU), down to 8 planes; a box that does not make 512 workgroups of 8-plane
 // runs takes yee_step's 16x4x4 tiles, which have no chain.  Measured with
-// tiles and with runs of 8, 16 and 32 planes: 128x64x64 25, 29, 42, 69 us;
-// 160x96x96 54, 47, 52, 70 us; 256x128x128 197, 124, 119, 127 us;
-// 512x256x256 1456, 819, 753, 728 us.
+// tiles and with runs of 8, 16 and 32 planes: 128x64x64 22, 29, 42, 69 us;
+// 160x96x96 46, 47, 52, 70 us; 256x128x128 205, 124, 119, 127 us;
+// 512x256x256 1483, 819, 753, 728 us.
 struct MarchTile { static constexpr int X = 32, Y = 8; };
 constexpr int kMarchMin = 8, kMarchMax = 32;
 
@@ -101,10 +109,13 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
                                                    const StoreDesc* __restrict__ plan, int nplan, int npx) {
   if (plan_block(plan, nplan, npx, par)) return;
   using T = YeeTile<DIM>;
-  constexpr int EXM = T::X + 3, EYM = T::Y + 3, EZM = DIM == 3 ? T::Z + 3 : 1;
-  constexpr int BXM = T::X + 2, BYM = T::Y + 2, BZM = DIM == 3 ? T::Z + 2 : 1;
-  __shared__ float sE[3][EZM * EYM * EXM];
-  __shared__ float sB[3][BZM * BYM * BXM];
+  // regions of a whole tile; an edge tile uses their first nodes of each axis
+  constexpr int EX = T::X + 3, EY = T::Y + 3, EZ = DIM == 3 ? T::Z + 3 : 1;
+  constexpr int BX = T::X + 2, BY = T::Y + 2, BZ = DIM == 3 ? T::Z + 2 : 1;
+  constexpr int EXY = EX * EY, BXY = BX * BY;
+  constexpr int NX = T::X + 1, NY = T::Y + 1, NZ = DIM == 3 ? T::Z + 1 : 1;  // nodes of E'
+  __shared__ float sE[3][EZ * EXY];
+  __shared__ float sB[3][BZ * BXY];
   const InstDesc& I = inst[blockIdx.y];
   const GridDesc& g = I.g;
   if (g.cyl) return;  // r-z instances take yee_step_rz
@@ -126,8 +137,6 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
     const int e0 = min(T::X, n0 - o0);
     const int e1 = min(T::Y, n1 - o1);
     const int e2 = DIM == 3 ? min(T::Z, n2 - o2) : 1;
-    const int EX = e0 + 3, EY = e1 + 3, EZ = DIM == 3 ? e2 + 3 : 1;
-    const int BX = e0 + 2, BY = e1 + 2, BZ = DIM == 3 ? e2 + 2 : 1;
     const int zoff = DIM == 3 ? 1 : 0;  // region origin is one node below the tile
     // moving window: the window column of region x index x (the x1 neighbour
     // beyond the window's front or back is zero), and whether the window
@@ -152,132 +161,134 @@ __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ 
       return gx + n0 * (gy + n1 * gz);
     };
     const gfloat* F = (const gfloat*)I.F[par];
-    // staging: the region's nodes in flat order, U per thread and round,
-    // every load of a round issued before its first LDS write (so a thread
-    // waits for memory once per round, not once per node and field)
+    // The current of the thread's E' nodes, U of them in flat order: loaded
+    // first, so that it is in flight with the staging instead of being waited
+    // for after two barriers.
+    constexpr int U = (NX * NY * NZ + kBlock - 1) / kBlock;
+    const int jp = par, jn = 1 - par;
+    float J[U][3];
+    int ji[U];  // the node's global index, -1: none
     {
-      constexpr int U = DIM == 3 ? 4 : 2;
-      const int EN = EX * EY * EZ;
-      for (int q0 = threadIdx.x; q0 < EN; q0 += U * kBlock) {
-        float v[U][6];
-        int rb[U];
+      const double jinv = (double)g.jinv;
+      const gfloat* Js = (const gfloat*)(I.sm_npass > 0 ? I.Jsm[(I.sm_npass - 1) & 1] : I.Jacc[jp]);
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-          const int q = q0 + u * kBlock;
-          rb[u] = -2;  // -2: no node, -1: node outside the B region
-          if (q < EN) {
-            const int x = q % EX, y = (q / EX) % EY, z = DIM == 3 ? q / (EX * EY) : 0;
-            const int gi = gidx(x, y, z);
-            v[u][0] = F[gi];
-            v[u][1] = F[nc + gi];
-            v[u][2] = F[2 * nc + gi];
-            rb[u] = -1;
-            if (x < BX && y < BY && z < BZ) {
-              rb[u] = x + BX * (y + BY * z);
-              v[u][3] = F[3 * nc + gi];
-              v[u][4] = F[4 * nc + gi];
-              v[u][5] = F[5 * nc + gi];
-            }
-          }
+      for (int u = 0; u < U; u++) {
+        const int q = threadIdx.x + u * kBlock;
+        const int x = 1 + q % NX, y = 1 + (q / NX) % NY, z = zoff + q / (NX * NY);
+        ji[u] = -1;
+        if (q >= NX * NY * NZ || x > e0 + 1 || y > e1 + 1 || (DIM == 3 && z > e2 + 1)) continue;
+        ji[u] = gidx(x, y, z);
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+          J[u][c] = I.sm_npass == 0 && g.acc_mode == 2 ? (float)((double)(long long)I.J64[jp][c * nc + ji[u]] * jinv)
+                                                       : Js[c * nc + ji[u]];
+      }
+    }
+    // staging: the region's nodes in flat order, all of a thread's loads
+    // issued before its first LDS write (so it waits for memory once)
+    {
+      constexpr int V = (EZ * EXY + kBlock - 1) / kBlock;
+      float v[V][6];
+      int rb[V];
+#pragma unroll
+      for (int u = 0; u < V; u++) {
+        const int q = threadIdx.x + u * kBlock;
+        const int x = q % EX, y = (q / EX) % EY, z = q / EXY;
+        rb[u] = -2;  // -2: no node, -1: node outside the B region
+        if (q >= EZ * EXY || x >= e0 + 3 || y >= e1 + 3 || (DIM == 3 && z >= e2 + 3)) continue;
+        const int gi = gidx(x, y, z);
+        v[u][0] = F[gi];
+        v[u][1] = F[nc + gi];
+        v[u][2] = F[2 * nc + gi];
+        rb[u] = -1;
+        if (x < e0 + 2 && y < e1 + 2 && (DIM == 2 || z < e2 + 2)) {
+          rb[u] = x + BX * (y + BY * z);
+          v[u][3] = F[3 * nc + gi];
+          v[u][4] = F[4 * nc + gi];
+          v[u][5] = F[5 * nc + gi];
         }
+      }
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-          const int q = q0 + u * kBlock;  // region index x + EX (y + EY z)
-          if (rb[u] == -2) continue;
-          sE[0][q] = v[u][0];
-          sE[1][q] = v[u][1];
-          sE[2][q] = v[u][2];
-          if (rb[u] >= 0) {
-            sB[0][rb[u]] = v[u][3];
-            sB[1][rb[u]] = v[u][4];
-            sB[2][rb[u]] = v[u][5];
-          }
+      for (int u = 0; u < V; u++) {
+        const int q = threadIdx.x + u * kBlock;  // region index x + EX (y + EY z)
+        if (rb[u] == -2) continue;
+        sE[0][q] = v[u][0];
+        sE[1][q] = v[u][1];
+        sE[2][q] = v[u][2];
+        if (rb[u] >= 0) {
+          sB[0][rb[u]] = v[u][3];
+          sB[1][rb[u]] = v[u][4];
+          sB[2][rb[u]] = v[u][5];
         }
       }
     }
     __syncthreads();
     const float h = 0.5f * g.dt;
     const float r0 = g.rdx[0], r1 = g.rdx[1], r2 = g.rdx[2];
-    const int EXY = EX * EY;
-    // Bh on the whole B region
-    for (int z = (DIM == 3 ? tz : 0); z < BZ; z += T::Z)
-      for (int y = ty; y < BY; y += T::Y)
-        for (int x = tx; x < BX; x += T::X) {
-          int r = x + BX * (y + BY * z);
-          int c = x + EX * (y + EY * z);
-          const bool front = win && wcol(x) == n0 - 1;
-          float d2E3 = (sE[2][c + EX] - sE[2][c]) * r1;
-          float d1E3 = ((front ? 0.0f : sE[2][c + 1]) - sE[2][c]) * r0;
-          float d1E2 = ((front ? 0.0f : sE[1][c + 1]) - sE[1][c]) * r0;
-          float d2E1 = (sE[0][c + EX] - sE[0][c]) * r1;
-          float d3E2 = 0.0f, d3E1 = 0.0f;
-          if (DIM == 3) {
-            d3E2 = (sE[1][c + EXY] - sE[1][c]) * r2;
-            d3E1 = (sE[0][c + EXY] - sE[0][c]) * r2;
-          }
-          sB[0][r] -= h * (d2E3 - d3E2);
-          sB[1][r] -= h * (d3E1 - d1E3);
-          sB[2][r] -= h * (d1E2 - d2E1);
-        }
+    // Bh on the whole B region, in flat order
+#pragma unroll
+    for (int q0 = 0; q0 < BZ * BXY; q0 += kBlock) {
+      const int r = q0 + threadIdx.x;
+      const int x = r % BX, y = (r / BX) % BY, z = r / BXY;
+      if (r >= BZ * BXY || x >= e0 + 2 || y >= e1 + 2 || (DIM == 3 && z >= e2 + 2)) continue;
+      const int c = x + EX * (y + EY * z);
+      const bool front = win && wcol(x) == n0 - 1;
+      float d2E3 = (sE[2][c + EX] - sE[2][c]) * r1;
+      float d1E3 = ((front ? 0.0f : sE[2][c + 1]) - sE[2][c]) * r0;
+      float d1E2 = ((front ? 0.0f : sE[1][c + 1]) - sE[1][c]) * r0;
+      float d2E1 = (sE[0][c + EX] - sE[0][c]) * r1;
+      float d3E2 = 0.0f, d3E1 = 0.0f;
+      if (DIM == 3) {
+        d3E2 = (sE[1][c + EXY] - sE[1][c]) * r2;
+        d3E1 = (sE[0][c + EXY] - sE[0][c]) * r2;
+      }
+      sB[0][r] -= h * (d2E3 - d3E2);
+      sB[1][r] -= h * (d3E1 - d1E3);
+      sB[2][r] -= h * (d1E2 - d2E1);
+    }
     __syncthreads();
     // E' on the tile plus one node above: region nodes 1 .. e+1 per axis
-    const int jp = par, jn = 1 - par;
-    const double jinv = (double)g.jinv;
-    const int BXY = BX * BY;
-    for (int z = zoff + (DIM == 3 ? tz : 0); z <= (DIM == 3 ? e2 + 1 : 0); z += T::Z)
-      for (int y = 1 + ty; y <= e1 + 1; y += T::Y)
-        for (int x = 1 + tx; x <= e0 + 1; x += T::X) {
-          int ce = x + EX * (y + EY * z);
-          int cb = x + BX * (y + BY * z);
-          int gi = gidx(x, y, z);
-          float J1, J2, J3;
-          if (I.sm_npass > 0) {
-            const gfloat* Js = (const gfloat*)I.Jsm[(I.sm_npass - 1) & 1];
-            J1 = Js[gi];
-            J2 = Js[nc + gi];
-            J3 = Js[2 * nc + gi];
-          } else if (g.acc_mode == 2) {
-            J1 = (float)((double)(long long)I.J64[jp][gi] * jinv);
-            J2 = (float)((double)(long long)I.J64[jp][nc + gi] * jinv);
-            J3 = (float)((double)(long long)I.J64[jp][2 * nc + gi] * jinv);
-          } else {
-            const gfloat* Ja = (const gfloat*)I.Jacc[jp];
-            J1 = Ja[gi];
-            J2 = Ja[nc + gi];
-            J3 = Ja[2 * nc + gi];
-          }
-          const bool back = win && wcol(x) == 0;
-          float d2B3 = (sB[2][cb] - sB[2][cb - BX]) * r1;
-          float d1B3 = (sB[2][cb] - (back ? 0.0f : sB[2][cb - 1])) * r0;
-          float d1B2 = (sB[1][cb] - (back ? 0.0f : sB[1][cb - 1])) * r0;
-          float d2B1 = (sB[0][cb] - sB[0][cb - BX]) * r1;
-          float d3B2 = 0.0f, d3B1 = 0.0f;
-          if (DIM == 3) {
-            d3B2 = (sB[1][cb] - sB[1][cb - BXY]) * r2;
-            d3B1 = (sB[0][cb] - sB[0][cb - BXY]) * r2;
-          }
-          sE[0][ce] += g.dt * ((d2B3 - d3B2) - J1);
-          sE[1][ce] += g.dt * ((d3B1 - d1B3) - J2);
-          sE[2][ce] += g.dt * ((d1B2 - d2B1) - J3);
-          // the tile's own cells: keep the step's current and clear the other accumulator
-          if (x <= e0 && y <= e1 && (DIM == 2 || z <= e2)) {
-            gfloat* Jo = (gfloat*)I.Jout;
-            const float keep = (back && wshift) ? 0.0f : 1.0f;  // discarded column
-            Jo[gi] = J1 * keep;
-            Jo[nc + gi] = J2 * keep;
-            Jo[2 * nc + gi] = J3 * keep;
-            if (g.acc_mode == 2) {
-              I.J64[jn][gi] = 0ull;
-              I.J64[jn][nc + gi] = 0ull;
-              I.J64[jn][2 * nc + gi] = 0ull;
-            } else {
-              gfloat* Jz = (gfloat*)I.Jacc[jn];
-              Jz[gi] = 0.0f;
-              Jz[nc + gi] = 0.0f;
-              Jz[2 * nc + gi] = 0.0f;
-            }
-          }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      if (ji[u] < 0) continue;
+      const int q = threadIdx.x + u * kBlock;
+      const int x = 1 + q % NX, y = 1 + (q / NX) % NY, z = zoff + q / (NX * NY);
+      const int ce = x + EX * (y + EY * z);
+      const int cb = x + BX * (y + BY * z);
+      const int gi = ji[u];
+      const float J1 = J[u][0], J2 = J[u][1], J3 = J[u][2];
+      const bool back = win && wcol(x) == 0;
+      float d2B3 = (sB[2][cb] - sB[2][cb - BX]) * r1;
+      float d1B3 = (sB[2][cb] - (back ? 0.0f : sB[2][cb - 1])) * r0;
+      float d1B2 = (sB[1][cb] - (back ? 0.0f : sB[1][cb - 1])) * r0;
+      float d2B1 = (sB[0][cb] - sB[0][cb - BX]) * r1;
+      float d3B2 = 0.0f, d3B1 = 0.0f;
+      if (DIM == 3) {
+        d3B2 = (sB[1][cb] - sB[1][cb - BXY]) * r2;
+        d3B1 = (sB[0][cb] - sB[0][cb - BXY]) * r2;
+      }
+      sE[0][ce] += g.dt * ((d2B3 - d3B2) - J1);
+      sE[1][ce] += g.dt * ((d3B1 - d1B3) - J2);
+      sE[2][ce] += g.dt * ((d1B2 - d2B1) - J3);
+      // the tile's own cells: keep the step's current and clear the other accumulator
+      if (x <= e0 && y <= e1 && (DIM == 2 || z <= e2)) {
+        gfloat* Jo = (gfloat*)I.Jout;
+        const float keep = (back && wshift) ? 0.0f : 1.0f;  // discarded column
+        Jo[gi] = J1 * keep;
+        Jo[nc + gi] = J2 * keep;
+        Jo[2 * nc + gi] = J3 * keep;
+        if (g.acc_mode == 2) {
+          I.J64[jn][gi] = 0ull;
+          I.J64[jn][nc + gi] = 0ull;
+          I.J64[jn][2 * nc + gi] = 0ull;
+        } else {
+          gfloat* Jz = (gfloat*)I.Jacc[jn];
+          Jz[gi] = 0.0f;
+          Jz[nc + gi] = 0.0f;
+          Jz[2 * nc + gi] = 0.0f;
         }
+      }
+    }
     __syncthreads();
     // B' on the tile, and write E', B' back; the largest |E'_c| written
     // raises the instance's running field bound (read by the particle
@@ -611,10 +622,11 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
                                                    const StoreDesc* __restrict__ plan, int nplan, int npx) {
   if (plan_block(plan, nplan, npx, par)) return;
   using T = YeeTile<2>;
-  constexpr int EXM = T::X + 3, EYM = T::Y + 3;
-  constexpr int BXM = T::X + 2, BYM = T::Y + 2;
-  __shared__ float sE[3][EYM * EXM];
-  __shared__ float sB[3][BYM * BXM];
+  constexpr int EX = T::X + 3, EY = T::Y + 3;
+  constexpr int BX = T::X + 2, BY = T::Y + 2;
+  constexpr int NX = T::X + 1, NY = T::Y + 1;  // nodes of E'
+  __shared__ float sE[3][EY * EX];
+  __shared__ float sB[3][BY * BX];
   const InstDesc& I = inst[blockIdx.y];
   const GridDesc& g = I.g;
   if (!g.cyl) return;
@@ -630,8 +642,6 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
   const int o1 = (tile / ntx) * T::Y;
   const int e0 = min(T::X, n0 - o0);
   const int e1 = min(T::Y, n1 - o1);
-  const int EX = e0 + 3, EY = e1 + 3;
-  const int BX = e0 + 2, BY = e1 + 2;
   // moving window along z: the window column of region column x; the z
   // neighbours beyond the window's front and back are zero, and the back
   // column is discarded (becomes the empty front) after a shift
@@ -648,24 +658,44 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
     int r = wrap1(o0 - 1 + x, n0) - wo;
     return r < 0 ? r + n0 : r;
   };
-  // region node (x, y) is column o0 - 1 + x (periodic) and row o1 - 1 + y.
-  // Staged in flat order, two nodes per thread with every load in flight
-  // before the first LDS write, so a workgroup waits here for one memory
-  // latency instead of up to four: 4.3 us a step less on a box of 384x96 (144
-  // workgroups; the kernel took 15.3 us before).
   const gfloat* F = (const gfloat*)I.F[par];
+  // region node (x, y) is column o0 - 1 + x (periodic) and row o1 - 1 + y.
+  // The current of the E' nodes is loaded with the staging, in flat order (as
+  // in yee_step).
+  constexpr int U = (EX * EY + kBlock - 1) / kBlock;
+  const int jp = par, jn = 1 - par;
+  float J[U][3];
+  int ji[U];  // the node's global index, -1: at or beyond the wall, -2: no node
   {
-    constexpr int U = 2;  // EXM * EYM <= U * kBlock
-    static_assert(EXM * EYM <= U * kBlock, "one round stages the region");
-    const int EN = EX * EY;
+    const double jinv = (double)g.jinv;
+    const gfloat* Js = (const gfloat*)(I.sm_npass > 0 ? I.Jsm[(I.sm_npass - 1) & 1] : I.Jacc[jp]);
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      const int q = threadIdx.x + k * kBlock;
+      const int x = 1 + q % NX, y = 1 + q / NX;
+      const int j = o1 - 1 + y;
+      ji[k] = -2;
+      if (q >= NX * NY || x > e0 + 1 || y > e1 + 1) continue;
+      ji[k] = -1;
+      if (j >= n1) continue;
+      ji[k] = wrap1(o0 - 1 + x, n0) + n0 * j;
+#pragma unroll
+      for (int c = 0; c < 3; c++)
+        J[k][c] = I.sm_npass == 0 && g.acc_mode == 2 ? (float)((double)(long long)I.J64[jp][c * nc + ji[k]] * jinv)
+                                                     : Js[c * nc + ji[k]];
+    }
+  }
+  // the fields, two nodes per thread with every load in flight before the
+  // first LDS write
+  {
     float v[U][6];
     int rb[U];
 #pragma unroll
     for (int k = 0; k < U; k++) {
       const int q = threadIdx.x + k * kBlock;
-      rb[k] = -1;
-      if (q < EN) {
-        const int x = q % EX, y = q / EX;
+      const int x = q % EX, y = q / EX;
+      rb[k] = -2;  // -2: no node, -1: node outside the B region
+      if (q < EX * EY && x < e0 + 3 && y < e1 + 3) {
         const int gx = wrap1(o0 - 1 + x, n0);
         const int ry = o1 - 1 + y;
         const int rw = ry <= 0 ? 1 - ry : ry;
@@ -676,7 +706,8 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
         v[k][0] = iw ? F[gw] : 0.0f;
         v[k][1] = ih ? sh * F[nc + gh] : 0.0f;
         v[k][2] = iw ? sw * F[2 * nc + gw] : 0.0f;
-        if (x < BX && y < BY) {
+        rb[k] = -1;
+        if (x < e0 + 2 && y < e1 + 2) {
           rb[k] = x + BX * y;
           v[k][3] = ih ? F[3 * nc + gh] : 0.0f;
           v[k][4] = iw ? sw * F[4 * nc + gw] : 0.0f;
@@ -687,7 +718,7 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
 #pragma unroll
     for (int k = 0; k < U; k++) {
       const int q = threadIdx.x + k * kBlock;
-      if (q >= EN) continue;
+      if (rb[k] == -2) continue;
       sE[0][q] = v[k][0];
       sE[1][q] = v[k][1];
       sE[2][q] = v[k][2];
@@ -703,82 +734,74 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
   const float rz = g.rdx[0], rr = g.rdx[1];
   // Bh on the B region (B_z, B_theta on half rows, B_r on whole rows); the
   // general r weights also give the mirror rows below the axis their images
-  for (int y = ty; y < BY; y += T::Y)
-    for (int x = tx; x < BX; x += T::X) {
-      const int r = x + BX * y;
-      const int c = x + EX * y;
-      const int j = o1 - 1 + y;
-      const bool front = win && wcol(x) == n0 - 1;
-      sB[1][r] -= h * (-((front ? 0.0f : sE[2][c + 1]) - sE[2][c]) * rz);
-      sB[2][r] -= h * (((front ? 0.0f : sE[1][c + 1]) - sE[1][c]) * rz - (sE[0][c + EX] - sE[0][c]) * rr);
-      const float cz = j == 0 ? 4.0f * sE[2][c + EX] * rr
-                              : ((j + 0.5f) * sE[2][c + EX] - (j - 0.5f) * sE[2][c]) * rr / (float)j;
-      sB[0][r] -= h * cz;
-    }
+#pragma unroll
+  for (int q0 = 0; q0 < BY * BX; q0 += kBlock) {
+    const int r = q0 + threadIdx.x;
+    const int x = r % BX, y = r / BX;
+    if (r >= BY * BX || x >= e0 + 2 || y >= e1 + 2) continue;
+    const int c = x + EX * y;
+    const int j = o1 - 1 + y;
+    const bool front = win && wcol(x) == n0 - 1;
+    sB[1][r] -= h * (-((front ? 0.0f : sE[2][c + 1]) - sE[2][c]) * rz);
+    sB[2][r] -= h * (((front ? 0.0f : sE[1][c + 1]) - sE[1][c]) * rz - (sE[0][c + EX] - sE[0][c]) * rr);
+    const float cz = j == 0 ? 4.0f * sE[2][c + EX] * rr
+                            : ((j + 0.5f) * sE[2][c + EX] - (j - 0.5f) * sE[2][c]) * rr / (float)j;
+    sB[0][r] -= h * cz;
+  }
   __syncthreads();
   // E' on the tile plus one node above (zero at and beyond the wall)
-  const int jp = par, jn = 1 - par;
-  const double jinv = (double)g.jinv;
-  for (int y = 1 + ty; y <= e1 + 1; y += T::Y)
-    for (int x = 1 + tx; x <= e0 + 1; x += T::X) {
-      const int ce = x + EX * y;
-      const int cb = x + BX * y;
-      const int j = o1 - 1 + y;
-      if (j >= n1) {
-        sE[0][ce] = 0.0f;
-        sE[1][ce] = 0.0f;
-        sE[2][ce] = 0.0f;
-        continue;
-      }
-      const int gi = wrap1(o0 - 1 + x, n0) + n0 * j;
-      float J1, J2, J3;
-      // ring volumes of the row: whole rows (j - 1/2), half rows j
-      const float vw = j >= 1 ? 1.0f / ((float)j - 0.5f) : 0.0f;
-      const float vh = j >= 1 ? 1.0f / (float)j : 0.0f;
-      if (I.sm_npass > 0) {  // the smoothed current is a density already
-        const gfloat* Js = (const gfloat*)I.Jsm[(I.sm_npass - 1) & 1];
-        const float on = j >= 1 ? 1.0f : 0.0f;
-        J1 = on * Js[gi];
-        J2 = on * Js[nc + gi];
-        J3 = on * Js[2 * nc + gi];
+#pragma unroll
+  for (int k = 0; k < U; k++) {
+    if (ji[k] == -2) continue;
+    const int q = threadIdx.x + k * kBlock;
+    const int x = 1 + q % NX, y = 1 + q / NX;
+    const int ce = x + EX * y;
+    const int cb = x + BX * y;
+    const int j = o1 - 1 + y;
+    if (ji[k] < 0) {
+      sE[0][ce] = 0.0f;
+      sE[1][ce] = 0.0f;
+      sE[2][ce] = 0.0f;
+      continue;
+    }
+    const int gi = ji[k];
+    float J1 = J[k][0], J2 = J[k][1], J3 = J[k][2];
+    // ring volumes of the row: whole rows (j - 1/2), half rows j
+    const float vw = j >= 1 ? 1.0f / ((float)j - 0.5f) : 0.0f;
+    const float vh = j >= 1 ? 1.0f / (float)j : 0.0f;
+    if (I.sm_npass > 0) {  // the smoothed current is a density already
+      const float on = j >= 1 ? 1.0f : 0.0f;
+      J1 = on * J1;
+      J2 = on * J2;
+      J3 = on * J3;
+    } else {
+      J1 *= vw;
+      J2 *= vh;
+      J3 *= vw;
+    }
+    const bool back = win && wcol(x) == 0;
+    const float bt_m = back ? 0.0f : sB[2][cb - 1], br_m = back ? 0.0f : sB[1][cb - 1];
+    sE[1][ce] = j == 0 ? 0.0f : sE[1][ce] + g.dt * (-(sB[2][cb] - bt_m) * rz - J2);
+    sE[2][ce] += g.dt * ((sB[1][cb] - br_m) * rz - (sB[0][cb] - sB[0][cb - BX]) * rr - J3);
+    sE[0][ce] += g.dt * (((float)j * sB[2][cb] - (float)(j - 1) * sB[2][cb - BX]) * rr * vw - J1);
+    if (x <= e0 && y <= e1) {
+      gfloat* Jo = (gfloat*)I.Jout;
+      const float keep = (back && wshift) ? 0.0f : 1.0f;  // discarded column
+      Jo[gi] = J1 * keep;
+      Jo[nc + gi] = J2 * keep;
+      Jo[2 * nc + gi] = J3 * keep;
+      if (g.acc_mode == 2) {
+        I.J64[jn][gi] = 0ull;
+        I.J64[jn][nc + gi] = 0ull;
+        I.J64[jn][2 * nc + gi] = 0ull;
       } else {
-        if (g.acc_mode == 2) {
-          J1 = (float)((double)(long long)I.J64[jp][gi] * jinv);
-          J2 = (float)((double)(long long)I.J64[jp][nc + gi] * jinv);
-          J3 = (float)((double)(long long)I.J64[jp][2 * nc + gi] * jinv);
-        } else {
-          const gfloat* Ja = (const gfloat*)I.Jacc[jp];
-          J1 = Ja[gi];
-          J2 = Ja[nc + gi];
-          J3 = Ja[2 * nc + gi];
-        }
-        J1 *= vw;
-        J2 *= vh;
-        J3 *= vw;
-      }
-      const bool back = win && wcol(x) == 0;
-      const float bt_m = back ? 0.0f : sB[2][cb - 1], br_m = back ? 0.0f : sB[1][cb - 1];
-      sE[1][ce] = j == 0 ? 0.0f : sE[1][ce] + g.dt * (-(sB[2][cb] - bt_m) * rz - J2);
-      sE[2][ce] += g.dt * ((sB[1][cb] - br_m) * rz - (sB[0][cb] - sB[0][cb - BX]) * rr - J3);
-      sE[0][ce] += g.dt * (((float)j * sB[2][cb] - (float)(j - 1) * sB[2][cb - BX]) * rr * vw - J1);
-      if (x <= e0 && y <= e1) {
-        gfloat* Jo = (gfloat*)I.Jout;
-        const float keep = (back && wshift) ? 0.0f : 1.0f;  // discarded column
-        Jo[gi] = J1 * keep;
-        Jo[nc + gi] = J2 * keep;
-        Jo[2 * nc + gi] = J3 * keep;
-        if (g.acc_mode == 2) {
-          I.J64[jn][gi] = 0ull;
-          I.J64[jn][nc + gi] = 0ull;
-          I.J64[jn][2 * nc + gi] = 0ull;
-        } else {
-          gfloat* Jz = (gfloat*)I.Jacc[jn];
-          Jz[gi] = 0.0f;
-          Jz[nc + gi] = 0.0f;
-          Jz[2 * nc + gi] = 0.0f;
-        }
+        gfloat* Jz = (gfloat*)I.Jacc[jn];
+        Jz[gi] = 0.0f;
+        Jz[nc + gi] = 0.0f;
+        Jz[2 * nc + gi] = 0.0f;
       }
     }
+  }
   __syncthreads();
   // B' on the tile, and write E', B' back
   gfloat* Fw = (gfloat*)I.F[1 - par];
