@@ -2,10 +2,11 @@
 //
 // A Sim holds one or more independent periodic instances.  A plain context is
 // a Sim of one instance; a batch is a Sim of many.  Each step launches, for
-// all instances together: current reset, the fused particle kernel (one
-// launch per dimension/shape-order group), the three Yee kernels, and every
-// sort_interval steps the conditional tile rebin.  pic_step replays captured
-// HIP graphs of whole rebin cycles.
+// all instances together: the fused particle kernel (one launch per group of
+// dimension, shape order and boundary logic), the current smoothing where
+// asked for, the field step (one launch per dimension, which also plans a
+// rebin check), and every sort_interval steps the rebin's scatter.  pic_step
+// replays captured HIP graphs of whole rebin cycles.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
