@@ -2093,15 +2093,28 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
       }
       s_cur[s] = pic_cur(*S.ctl) | e << 1;
     }
-  if (threadIdx.x == 0) {
+  // (a store per lane: one thread walking the control words waited for them
+  // once per store; a batch of 24 instances 119 -> 115 us, order 1, and
+  // 91 -> 88, order 2; the scatter's likewise, 41 -> 36 us)
+  if (threadIdx.x < 64) {
     int acc = 0;
-    for (int s = 0; s < nstores; s++) {
-      const int cur = pic_cur(*stores[s].ctl);
-      if (MODE > 1) s_cur[s] = cur;
-      s_pref[s] = acc;
-      acc += stores[s].ctl->n_items[cur];
+    for (int base = 0; base < nstores; base += 64) {
+      const int s = base + (int)threadIdx.x;
+      int n = 0;
+      if (s < nstores) {
+        const int cur = pic_cur(*stores[s].ctl);
+        if (MODE > 1) s_cur[s] = cur;
+        n = stores[s].ctl->n_items[cur];
+      }
+      int sum = n;
+      for (int off = 1; off < 64 && off < nstores; off <<= 1) {
+        const int v = __shfl_up(sum, off);
+        if ((int)threadIdx.x >= off) sum += v;
+      }
+      if (s < nstores) s_pref[s + 1] = acc + sum;
+      acc += __shfl(sum, 63);
     }
-    s_pref[nstores] = acc;
+    if (threadIdx.x == 0) s_pref[0] = 0;
   }
   __syncthreads();
   const int total = s_pref[nstores];
@@ -2119,7 +2132,12 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
     first = lo + (int)(blockIdx.x >> 3);
     stride = gridDim.x >> 3;
   }
-  int s = 0;
+  int s = 0;  // the store of the first item
+  for (int top = nstores - 1; s < top;) {
+    const int mid = (s + top + 1) >> 1;
+    if (s_pref[mid] <= first) s = mid;
+    else top = mid - 1;
+  }
   for (int gi = first; gi < hi; gi += stride) {
     while (gi >= s_pref[s + 1]) s++;
     // the store, its buffer set and the item are the workgroup's own: read

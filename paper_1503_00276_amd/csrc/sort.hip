@@ -133,13 +133,21 @@ __global__ void __launch_bounds__(kBlock) rebin_offsets(const StoreDesc* __restr
 // Block-shared prefix over stores of a per-store count (0 for idle stores).
 template <typename F>
 __device__ void group_prefix(const StoreDesc* stores, int nstores, int* pref, F count) {
-  if (threadIdx.x == 0) {
+  // a store per lane: one thread walking the control words would wait for them
+  // once per store
+  if (threadIdx.x < 64) {
     int acc = 0;
-    for (int s = 0; s < nstores; s++) {
-      pref[s] = acc;
-      acc += stores[s].ctl->active ? count(stores[s]) : 0;
+    for (int base = 0; base < nstores; base += 64) {
+      const int s = base + (int)threadIdx.x;
+      int sum = s < nstores && stores[s].ctl->active ? count(stores[s]) : 0;
+      for (int off = 1; off < 64 && off < nstores; off <<= 1) {
+        const int v = __shfl_up(sum, off);
+        if ((int)threadIdx.x >= off) sum += v;
+      }
+      if (s < nstores) pref[s + 1] = acc + sum;
+      acc += __shfl(sum, 63);
     }
-    pref[nstores] = acc;
+    if (threadIdx.x == 0) pref[0] = 0;
   }
   __syncthreads();
 }
@@ -176,7 +184,7 @@ __global__ void __launch_bounds__(kBlock) rebin_scatter(const StoreDesc* __restr
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  int s = 0;
+  int s = (int)blockIdx.x < total ? store_of(pref, nstores, blockIdx.x) : 0;
   for (int gi = blockIdx.x; gi < total; gi += gridDim.x) {
     while (gi >= pref[s + 1]) s++;
     const StoreDesc& S = stores[s];
