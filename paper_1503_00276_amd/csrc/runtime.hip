@@ -225,51 +225,70 @@ double default_tile_cells(const GridDesc& g, int64_t total, double ppc) {
 // of multiples of four in 3D (the cells of a wavefront then spread over the LDS
 // banks; the 4x4xN strides are compile-time constants).  Extents that do not
 // divide the axis are taken too: an axis of 37 or 53 cells used to become one
-// tile (45x37x53, linear: 120 us in 3x17x25 tiles, 43 us in 9x8x8).  Returns
-// false when no shape is valid.
+// tile (45x37x53, linear: 120 us in 3x17x25 tiles, 43 us in 9x8x8).
+// Where none of those shapes does (a cubic 3D window, an asked-for long tile, a
+// long interval: the halo alone fills half the LDS), any extent whose LDS one
+// workgroup can have is looked at, so that a box is refused only if no tile
+// fits it.  Returns false when no shape does.
 bool default_tile(const GridDesc& g0, const pic_config& c, double cells, int out[3]) {
   struct Extent {
     int t;
     double lg, cost;  // log2 of the mean extent; what the extent itself costs
   };
-  GridDesc g = g0;
-  std::vector<Extent> cand[3];
-  for (int d = 0; d < 3; d++) {
-    const int need = g.slk[d] + 2, n = g.nx[d];
-    auto add = [&](int t) {
-      double cost = n % t != 0 ? 0.05 : 0.0;
-      if (g.dim == 3 && t % 4 != 0) cost += 0.15;
-      cand[d].push_back({t, std::log2((double)n / ((n + t - 1) / t)), cost});
-    };
-    if (d >= g.dim) {
-      add(1);
-    } else if (c.tile[d] != 0) {
-      if (c.tile[d] > 0) add(c.tile[d]);
-    } else {
-      const int most = g.dim == 3 ? 16 : 64;
-      for (int t = need; t < n && t <= most; t++)
-        if (tile_ok(n, t, need)) add(t);
-      if (n <= most || cand[d].empty()) add(n);
-    }
-  }
   const double want = std::log2(cells);
-  const double aspect = g.dim == 3 ? 0.0 : (pic_gpd_two_phase2(g) ? (cells >= 192.0 ? 1.6 : 0.5) : 0.0);
+  const double aspect = g0.dim == 3 ? 0.0 : (pic_gpd_two_phase2(g0) ? (cells >= 192.0 ? 1.6 : 0.5) : 0.0);
   double best = 1e300;
-  for (const Extent& a : cand[0])
-    for (const Extent& b : cand[1])
-      for (const Extent& e : cand[2]) {
-        double sc = a.cost + b.cost + (g.dim == 3 ? e.cost : 0.0) + std::fabs(a.lg + b.lg + e.lg - want) +
-                    0.1 * std::fabs(a.lg - b.lg - aspect);
-        if (g.dim == 3) sc += 0.1 * std::fabs(b.lg - e.lg) + 0.01 * (e.lg - a.lg);
-        if (sc >= best) continue;
-        g.tile[0] = a.t;
-        g.tile[1] = b.t;
-        g.tile[2] = e.t;
-        if (pic_gpd_split(g)) pic_gpd_split_strides(g);
-        if (pic_gpd_lds_bytes(g) > (size_t)kLdsMax / 2) continue;
-        best = sc;
-        for (int d = 0; d < 3; d++) out[d] = g.tile[d];
+  for (int pass = 0; pass < 2 && best == 1e300; pass++) {
+    const bool any = pass == 1;
+    const size_t room = any ? (size_t)kLdsMax : (size_t)kLdsMax / 2;
+    GridDesc g = g0;
+    // The field tile alone (every kernel stages it; the padded strides of the
+    // two-phase 3D kernel, which take a search, only add to it): an extent
+    // whose field tile is too large with the smallest extents of the other
+    // axes is left out.
+    auto fields = [&]() {
+      size_t n = 6 * sizeof(float);
+      for (int d = 0; d < g.dim; d++) n *= (size_t)(g.tile[d] + 2 * g.slk[d] + g.fa + g.fb);
+      return n;
+    };
+    int least[3] = {1, 1, 1};
+    for (int d = 0; d < g.dim; d++) least[d] = c.tile[d] != 0 ? c.tile[d] : std::min(g.nx[d], g.slk[d] + 2);
+    std::vector<Extent> cand[3];
+    for (int d = 0; d < 3; d++) {
+      const int need = g.slk[d] + 2, n = g.nx[d];
+      auto add = [&](int t) {
+        for (int k = 0; k < 3; k++) g.tile[k] = k == d ? t : least[k];
+        if (fields() > room) return;
+        double cost = n % t != 0 ? 0.05 : 0.0;
+        if (g.dim == 3 && t % 4 != 0) cost += 0.15;
+        cand[d].push_back({t, std::log2((double)n / ((n + t - 1) / t)), cost});
+      };
+      if (d >= g.dim) {
+        add(1);
+      } else if (c.tile[d] != 0) {
+        add(c.tile[d]);
+      } else {
+        const int most = any ? n : (g.dim == 3 ? 16 : 64);
+        for (int t = need; t < n && t <= most; t++)
+          if (tile_ok(n, t, need)) add(t);
+        if (n <= most || cand[d].empty()) add(n);
       }
+    }
+    for (const Extent& a : cand[0])
+      for (const Extent& b : cand[1])
+        for (const Extent& e : cand[2]) {
+          double sc = a.cost + b.cost + (g.dim == 3 ? e.cost : 0.0) + std::fabs(a.lg + b.lg + e.lg - want) +
+                      0.1 * std::fabs(a.lg - b.lg - aspect);
+          if (g.dim == 3) sc += 0.1 * std::fabs(b.lg - e.lg) + 0.01 * (e.lg - a.lg);
+          if (sc >= best) continue;
+          g.tile[0] = a.t;
+          g.tile[1] = b.t;
+          g.tile[2] = e.t;
+          if (fields() > room || pic_gpd_lds_bytes(g) > room) continue;
+          best = sc;
+          for (int d = 0; d < 3; d++) out[d] = g.tile[d];
+        }
+  }
   return best < 1e300;
 }
 
@@ -322,27 +341,24 @@ pic_status setup_grid(Sim& S, const pic_config& c, int sort_interval, GridDesc& 
     g.jb -= 1;
   }
   g.ntiles = 1;
-  int auto_tile[3] = {0, 0, 0};
+  int tile[3] = {1, 1, 1};
   bool any_auto = false;
-  for (int d = 0; d < c.ndim; d++) any_auto = any_auto || c.tile[d] == 0;
+  for (int d = 0; d < c.ndim; d++) {
+    const int need = g.slk[d] + 2;
+    tile[d] = c.tile[d];
+    any_auto = any_auto || tile[d] == 0;
+    if (tile[d] != 0 && !tile_ok(g.nx[d], tile[d], need))
+      return S.fail(PIC_E_INVALID, "tile[%d]=%d does not suit nx=%d (needs >= %d cells per tile and per remainder)",
+                    d, tile[d], g.nx[d], need);
+  }
   if (any_auto) {
     const int64_t total = std::max<int64_t>(S.total_cells, (int64_t)g.nx[0] * g.nx[1] * g.nx[2]);
-    if (!default_tile(g, c, default_tile_cells(g, total, ppc), auto_tile))
-      for (int d = 0; d < c.ndim; d++) auto_tile[d] = g.nx[d];  // shrunk below
+    if (!default_tile(g, c, default_tile_cells(g, total, ppc), tile))
+      return S.fail(PIC_E_INVALID, "no tile fits the LDS");
   }
   for (int d = 0; d < 3; d++) {
-    if (d >= c.ndim) {
-      g.tile[d] = 1;
-      g.ntile[d] = 1;
-      continue;
-    }
-    const int need = g.slk[d] + 2;
-    const int t = c.tile[d] != 0 ? c.tile[d] : auto_tile[d];
-    if (!tile_ok(g.nx[d], t, need))
-      return S.fail(PIC_E_INVALID, "tile[%d]=%d does not suit nx=%d (needs >= %d cells per tile and per remainder)",
-                    d, t, g.nx[d], need);
-    g.tile[d] = t;
-    g.ntile[d] = (g.nx[d] + t - 1) / t;
+    g.tile[d] = tile[d];
+    g.ntile[d] = (g.nx[d] + tile[d] - 1) / tile[d];
     g.ntiles *= g.ntile[d];
   }
   int b0 = bits_for(g.nx[0]), b1 = bits_for(g.nx[1]), b2 = bits_for(g.nx[2]);
@@ -353,22 +369,7 @@ pic_status setup_grid(Sim& S, const pic_config& c, int sort_interval, GridDesc& 
   g.m1 = (1 << b1) - 1;
   g.ncell = g.nx[0] * g.nx[1] * g.nx[2];
   if (pic_gpd_split(g)) pic_gpd_split_strides(g);
-  // 3D tiles shrink until the fused kernel's LDS fits one workgroup
-  while (pic_gpd_lds_bytes(g) > (size_t)kLdsMax) {
-    int dmax = 0;
-    for (int d = 1; d < c.ndim; d++)
-      if (g.tile[d] > g.tile[dmax]) dmax = d;
-    int t = g.tile[dmax] / 2;
-    const int need = g.slk[dmax] + 2;
-    if (c.tile[dmax] != 0 || t < need) return S.fail(PIC_E_INVALID, "tile needs more LDS than a workgroup has");
-    while (t >= need && !tile_ok(g.nx[dmax], t, need)) t--;
-    if (t < need) return S.fail(PIC_E_INVALID, "no tile fits the LDS");
-    g.ntiles /= g.ntile[dmax];
-    g.tile[dmax] = t;
-    g.ntile[dmax] = (g.nx[dmax] + t - 1) / t;
-    g.ntiles *= g.ntile[dmax];
-    if (pic_gpd_split(g)) pic_gpd_split_strides(g);
-  }
+  if (pic_gpd_lds_bytes(g) > (size_t)kLdsMax) return S.fail(PIC_E_INVALID, "tile needs more LDS than a workgroup has");
   return PIC_OK;
 }
 
