@@ -101,8 +101,9 @@ typedef struct {
   int64_t capacity;      /* maximum particles per species (num_par_max) */
   int32_t tile[3];       /* tile extent in cells; 0 = a default from the grid
                             (periodic 3D boxes: and from the particles per
-                            cell of the first load; pic_autotune searches it
-                            by measurement) */
+                            cell of everything loaded before the first step
+                            with particles, which settles it; pic_autotune
+                            searches it by measurement) */
   int32_t sort_interval; /* steps between rebin checks; 0 = a default from the
                             Courant number (searched by pic_autotune) */
   int32_t chunk;         /* maximum particles one workgroup takes from a tile;

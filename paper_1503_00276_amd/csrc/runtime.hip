@@ -60,6 +60,7 @@ struct Instance {
   double wmax[PIC_MAX_SPECIES] = {0, 0, 0, 0, 0, 0, 0, 0};
   double* rho_snap = nullptr;
   bool have_snap = false;
+  bool settled = false;  // a step has run with particles: the default tile stays
   Species sp[PIC_MAX_SPECIES];
   int64_t steps = 0;
 };
@@ -199,7 +200,7 @@ bool two_phase2(const pic_config& c) {
 // fields with a halo and folds its current, so tiles are large where there
 // are items enough to fill the chip, and small where there are not.
 //   3D, two-phase kernel: 512 particles per tile, from 64 to 256 cells (ppc is
-//     the mean particles per cell, known at the first load; 0 before).  96^3
+//     the mean particles per cell of what is loaded; 0 before, see tile_open).  96^3
 //     cells, us a step with 4x4x4 / 8x4x4 / 8x8x4 tiles: quadratic shape at
 //     1, 2, 4, 8 per cell 295 / 219 / 175, 313 / 242 / 223, 363 / 319 / 350,
 //     522 / 572 / 572; cubic 375 / 267 / 249, 405 / 319 / 330, 483 / 457 / 548,
@@ -858,10 +859,13 @@ pic_status capture_cycle(Sim& S, int par) {
   return PIC_OK;
 }
 
+pic_status settle_tiles(Sim& S);
+
 pic_status sim_step(Sim& S, int64_t nsteps) {
   if (nsteps < 0) return S.fail(PIC_E_INVALID, "nsteps < 0");
   if (nsteps == 0) return PIC_OK;
-  pic_status st = refresh_descriptors(S);
+  pic_status st = settle_tiles(S);
+  if (st == PIC_OK) st = refresh_descriptors(S);
   if (st != PIC_OK) return st;
   if (S.sgroups.empty() && S.igroups.empty()) return PIC_OK;
   const int SI = S.sort_interval;
@@ -1127,20 +1131,40 @@ pic_status copy_in(Sim& S, std::vector<double>& dst, const double* src, size_t n
 
 pic_status build_tables(Sim& S, Instance& I);
 
-// First load of an instance, before anything is binned: the default tile of a
-// periodic 3D box follows its particles per cell, and the neighbour table is
-// made for the tiles.
-pic_status first_load_tiles(Sim& S, Instance& I, int64_t n) {
-  if (I.ndst) return PIC_OK;
+int64_t instance_particles(const Instance& I);
+
+// Whether the library chooses the instance's tile by its particles per cell
+// (periodic 3D boxes without asked-for extents), and has not settled it yet.
+// Until the first step with particles, each load that finds the instance empty
+// chooses the tile, and that step chooses it again by everything loaded: a
+// driver bunch loaded before the plasma, or a plasma loaded in slices, looks
+// like a box of few particles per cell.
+bool tile_open(const Instance& I) {
   bool asked = false;
   for (int d = 0; d < I.g.dim; d++) asked = asked || I.cfg.tile[d] != 0;
-  if (pic_gpd_split(I.g) && !asked) {
-    GridDesc g;
-    pic_status st = setup_grid(S, I.cfg, S.sort_interval, g, (double)n / I.g.ncell);
-    if (st != PIC_OK) return st;
-    I.g = g;
-    S.dirty = true;
-  }
+  return !I.settled && !asked && pic_gpd_split(I.g);
+}
+
+// The grid n more particles would be loaded into; nothing of it is in force
+// before take_tiles.
+pic_status tiles_for(Sim& S, const Instance& I, int64_t n, GridDesc& g) {
+  g = I.g;
+  if (n == 0 || !tile_open(I) || instance_particles(I) > 0) return PIC_OK;
+  return setup_grid(S, I.cfg, S.sort_interval, g, (double)n / I.g.ncell);
+}
+
+bool same_tiles(const GridDesc& a, const GridDesc& b) {
+  return a.tile[0] == b.tile[0] && a.tile[1] == b.tile[1] && a.tile[2] == b.tile[2];
+}
+
+// Put the tiles of g in force in an instance without particles, once a load has
+// passed its checks; its stores, if any, are allocated anew.
+pic_status take_tiles(Sim& S, Instance& I, const GridDesc& g) {
+  if (same_tiles(g, I.g)) return I.ndst ? PIC_OK : build_tables(S, I);
+  for (Species& sp : I.sp)
+    if (sp.used) free_species(sp);
+  I.g = g;
+  S.dirty = true;
   return build_tables(S, I);
 }
 
@@ -1182,6 +1206,97 @@ float inject_umax(const Instance& I, int species) {
   return (float)(8.5718 * std::sqrt(3.0) * I.cfg.inject_uth * (1.0 + 1e-6));
 }
 
+// Device memory of a load: small ones use the diagnostics' scratch, large ones
+// memory of their own, freed at the end.
+struct LoadMem {
+  char* at = nullptr;
+  void* own = nullptr;
+  LoadMem() = default;
+  LoadMem(const LoadMem&) = delete;
+  LoadMem& operator=(const LoadMem&) = delete;
+  ~LoadMem() { (void)hipFree(own); }
+  bool get(Sim& S, size_t bytes) {
+    if (bytes <= ((size_t)64 << 20)) {
+      if (diag_scratch(S, bytes, &at) != PIC_OK) at = nullptr;
+    } else if (hipMalloc(&own, bytes) == hipSuccess) {
+      at = (char*)own;
+    } else {
+      own = nullptr;
+    }
+    if (!at) (void)hipGetLastError();
+    return at != nullptr;
+  }
+  char* take(size_t b) {
+    char* p = at;
+    at += align256(b);
+    return p;
+  }
+};
+
+size_t load_keys(const GridDesc& g) { return (size_t)g.ntiles * g.tile[0] * g.tile[1] * g.tile[2]; }
+
+// What load_args takes for a store of 'total' particles.
+size_t load_bytes(const GridDesc& g, int64_t total) {
+  return 256 + align256(load_keys(g) * 4) + align256((size_t)g.ntiles * 4) + 2 * align256((size_t)total * 4);
+}
+
+// A load of 'old' stored and n new particles into the tiles of g.
+LoadArgs load_args(const GridDesc& g, int64_t old, int64_t n, LoadMem& mem) {
+  LoadArgs A{};
+  A.g = g;
+  A.old = old;
+  A.n = n;
+  A.status = (LoadStatus*)mem.take(sizeof(LoadStatus));
+  static_assert(sizeof(LoadStatus) <= 256, "room for the status");
+  A.cells = (int*)mem.take(load_keys(g) * 4);
+  A.tiles = (int*)mem.take((size_t)g.ntiles * 4);
+  A.rank = (int*)mem.take((size_t)(old + n) * 4);
+  A.slot = (int*)mem.take((size_t)(old + n) * 4);
+  return A;
+}
+
+// The stored particles: buffer set 'cur' of d.
+void load_from(LoadArgs& A, const StoreDesc& d, int cur) {
+  A.ocell = d.cell[cur];
+  A.oid = d.id[cur];
+  for (int k = 0; k < 3; k++) {
+    A.oeps[k] = d.eps[cur][k];
+    A.ou[k] = d.u[cur][k];
+  }
+  A.ow = d.w[cur];
+}
+
+pic_status load_count(Sim& S, const LoadArgs& A, LoadStatus& ls) {
+  ls = LoadStatus{};
+  ls.first = ~0ull;
+  ls.idmax = -1;
+  HIPCHK(S, hipMemcpy(A.status, &ls, sizeof ls, hipMemcpyHostToDevice));
+  HIPCHK(S, hipMemsetAsync(A.cells, 0, load_keys(A.g) * 4, nullptr));
+  HIPCHK(S, pic_launch_load_count(A, nullptr));
+  HIPCHK(S, hipMemcpy(&ls, A.status, sizeof ls, hipMemcpyDeviceToHost));
+  return PIC_OK;
+}
+
+pic_status load_place(Sim& S, const LoadArgs& A, const Species& sp, int set, LoadStatus& ls) {
+  HIPCHK(S, pic_launch_load_place(A, sp.desc, set, nullptr));
+  HIPCHK(S, hipMemcpy(&ls, A.status, sizeof ls, hipMemcpyDeviceToHost));
+  if (ls.items > sp.max_items) return S.fail(PIC_E_NOMEM, "work item list overflow");
+  return PIC_OK;
+}
+
+// Control words of a store whose particles a load has put into buffer set 'set'.
+void load_ctl(StoreCtl& c, int set, const LoadStatus& ls) {
+  c.cur = set;
+  c.pending = c.flag = c.active = c.bad = 0;
+  c.n_items[set] = ls.items;
+  c.n_items[1 - set] = 0;
+  c.sorted = 1;  // binned exactly: every particle in its own tile
+  // the one-phase kernels' bound on |u| covers every particle of the store
+  double u2;
+  memcpy(&u2, &ls.u2, 8);
+  raise_umax(c, std::nextafter((float)(std::sqrt(u2) * (1.0 + 1e-6)), INFINITY));
+}
+
 // The load on the device.  *done stays false where the host's path has to take
 // the call: a state that is reported after the input's own checks, or too
 // little device memory for both the old and the new arrays.  The kernels run
@@ -1195,11 +1310,11 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
   const int64_t old = sp.np, total = old + n;
   if ((I.cfg.capacity > 0 && total > I.cfg.capacity) || total > 0x7fffff00LL) return PIC_OK;
   if (win && species != 0 && !I.sp[0].used) return PIC_OK;
-  if (first_load_tiles(S, I, n) != PIC_OK) return PIC_OK;
+  GridDesc g;
+  if (tiles_for(S, I, n, g) != PIC_OK) return PIC_OK;
   WinCtl wc;
   pic_status st = read_win(S, I, wc);
   if (st != PIC_OK) return st;
-  const GridDesc& g = I.g;
   // input the kernels can read: memory of this device, aligned; else a copy
   const double* in[3] = {x, u, w};
   size_t in_bytes[3] = {(size_t)n * g.dim * 8, (size_t)n * 24, (size_t)n * 8}, stage = 0;
@@ -1215,46 +1330,16 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
     }
     if (copy[k]) stage += align256(in_bytes[k]);
   }
-  const size_t nkey = (size_t)g.ntiles * g.tile[0] * g.tile[1] * g.tile[2];
-  const size_t bytes = 256 + align256(nkey * 4) + align256((size_t)g.ntiles * 4) + 2 * align256((size_t)total * 4) + stage;
-  // small loads use the diagnostics' scratch, large ones memory of their own
-  char* mem = nullptr;
-  void* own = nullptr;
-  if (bytes <= ((size_t)64 << 20)) {
-    if (diag_scratch(S, bytes, &mem) != PIC_OK) mem = nullptr;
-  } else if (hipMalloc(&own, bytes) == hipSuccess) {
-    mem = (char*)own;
-  }
-  if (!mem) {
-    (void)hipGetLastError();
-    return PIC_OK;
-  }
-  struct Free {
-    void* p;
-    ~Free() { (void)hipFree(p); }
-  } free_own{own};
+  LoadMem mem;
+  if (!mem.get(S, load_bytes(g, total) + stage)) return PIC_OK;
   *done = true;
-  LoadArgs A{};
-  A.g = g;
+  LoadArgs A = load_args(g, old, n, mem);
   for (int d = 0; d < 3; d++) A.xmin[d] = I.cfg.xmin[d];
   A.shifts = wc.shifts;
   A.origin = wc.origin;
-  A.old = old;
-  A.n = n;
-  auto take = [&](size_t b) {
-    char* p = mem;
-    mem += align256(b);
-    return p;
-  };
-  A.status = (LoadStatus*)take(sizeof(LoadStatus));
-  static_assert(sizeof(LoadStatus) <= 256, "room for the status");
-  A.cells = (int*)take(nkey * 4);
-  A.tiles = (int*)take((size_t)g.ntiles * 4);
-  A.rank = (int*)take((size_t)total * 4);
-  A.slot = (int*)take((size_t)total * 4);
   for (int k = 0; k < 3; k++)
     if (copy[k]) {
-      char* p = take(in_bytes[k]);
+      char* p = mem.take(in_bytes[k]);
       HIPCHK(S, hipMemcpy(p, in[k], in_bytes[k], (flags & PIC_DEVICE_PTRS) ? hipMemcpyDefault : hipMemcpyHostToDevice));
       in[k] = (const double*)p;
     }
@@ -1265,24 +1350,11 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
   int set = 0;
   if (old > 0) {
     c = host_ctl(S, sp);
-    const int cur = pic_cur(c);
-    const StoreDesc& d = sp.desc;
-    A.ocell = d.cell[cur];
-    A.oid = d.id[cur];
-    for (int k = 0; k < 3; k++) {
-      A.oeps[k] = d.eps[cur][k];
-      A.ou[k] = d.u[cur][k];
-    }
-    A.ow = d.w[cur];
-    set = 1 - cur;  // (the set read from stays as it is)
+    load_from(A, sp.desc, pic_cur(c));
+    set = 1 - pic_cur(c);  // (the set read from stays as it is)
   }
-  LoadStatus ls{};
-  ls.first = ~0ull;
-  ls.idmax = -1;
-  HIPCHK(S, hipMemcpy(A.status, &ls, sizeof ls, hipMemcpyHostToDevice));
-  HIPCHK(S, hipMemsetAsync(A.cells, 0, nkey * 4, nullptr));
-  HIPCHK(S, pic_launch_load_count(A, nullptr));
-  HIPCHK(S, hipMemcpy(&ls, A.status, sizeof ls, hipMemcpyDeviceToHost));
+  LoadStatus ls;
+  if ((st = load_count(S, A, ls)) != PIC_OK) return st;
   if (ls.flags & 1) return S.fail(PIC_E_RANGE, "non-finite position");
   if (ls.flags & 2) return S.fail(PIC_E_RANGE, "non-finite momentum");
   if (ls.flags & 4) return S.fail(PIC_E_RANGE, "non-finite weight");
@@ -1291,9 +1363,9 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
   if (ls.first != ~0ull)
     return (ls.first & 1) ? S.fail(PIC_E_RANGE, "particle radius outside [0, (nr - 1/2) dr)")
                           : S.fail(PIC_E_RANGE, "particle outside the moving window");
-  double u2, wm;
-  memcpy(&u2, &ls.u2, 8);
+  double wm;
   memcpy(&wm, &ls.w, 8);
+  if ((st = take_tiles(S, I, g)) != PIC_OK) return st;
   const int64_t want = wanted_capacity(I, species, total);
   Species keep;  // the arrays the load reads from, until it is done
   if (!sp.used || want > sp.cap) {
@@ -1316,18 +1388,10 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
     c = StoreCtl{};
   }
   settle_species(I, species, wm);
-  hipError_t e = pic_launch_load_place(A, sp.desc, set, nullptr);
-  if (e == hipSuccess) e = hipMemcpy(&ls, A.status, sizeof ls, hipMemcpyDeviceToHost);
+  st = load_place(S, A, sp, set, ls);
   for (void* p : keep.allocs) (void)hipFree(p);
-  HIPCHK(S, e);
-  if (ls.items > sp.max_items) return S.fail(PIC_E_NOMEM, "work item list overflow");
-  c.cur = set;
-  c.pending = c.flag = c.active = c.bad = 0;
-  c.n_items[set] = ls.items;
-  c.n_items[1 - set] = 0;
-  c.sorted = 1;  // binned exactly: every particle in its own tile
-  // the one-phase kernels' bound on |u| covers every particle of the store
-  raise_umax(c, std::nextafter((float)(std::sqrt(u2) * (1.0 + 1e-6)), INFINITY));
+  if (st != PIC_OK) return st;
+  load_ctl(c, set, ls);
   raise_umax(c, inject_umax(I, species));
   if (win || rz) c.np = (int)total;
   HIPCHK(S, hipMemcpy(sp.ctl, &c, sizeof c, hipMemcpyHostToDevice));
@@ -1371,7 +1435,6 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
   for (double v : hw)
     if (!std::isfinite(v)) return S.fail(PIC_E_RANGE, "non-finite weight");
   const int64_t total = sp.np + n;
-  if ((st = first_load_tiles(S, I, n)) != PIC_OK) return st;
   if (I.cfg.capacity > 0 && total > I.cfg.capacity)
     return S.fail(PIC_E_NOMEM, "species %d would hold %lld particles, capacity %lld", species, (long long)total,
                   (long long)I.cfg.capacity);
@@ -1432,6 +1495,8 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
   }
   double wm = 0.0;
   for (double v : hw) wm = std::max(wm, std::fabs(v));
+  GridDesc g;
+  if ((st = tiles_for(S, I, n, g)) != PIC_OK || (st = take_tiles(S, I, g)) != PIC_OK) return st;
   const int64_t want = wanted_capacity(I, species, total);
   if (!sp.used || want > sp.cap) {
     int64_t cap = I.cfg.capacity > 0 ? std::max<int64_t>(I.cfg.capacity, want) : want;
@@ -1456,6 +1521,93 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
     S.ctl_current = false;
   }
   return st;
+}
+
+// Move the stores of an instance into the tiles of g.  Where the memory does not
+// hold the old and the new arrays together, the tiles stay as they are.
+pic_status retile(Sim& S, Instance& I, const GridDesc& g) {
+  pic_status st = sim_sync(S);
+  if (st != PIC_OK) return st;
+  const GridDesc g0 = I.g;
+  int* const ndst0 = I.ndst;
+  Species keep[PIC_MAX_SPECIES];
+  StoreCtl ctl[PIC_MAX_SPECIES];
+  int64_t most = 0;
+  for (int s = 0; s < PIC_MAX_SPECIES; s++) {
+    Species& sp = I.sp[s];
+    if (!sp.used) continue;
+    if (sp.np == 0) free_species(sp);  // (allocated at its next load)
+    keep[s] = sp;
+    if (sp.np == 0) continue;
+    ctl[s] = host_ctl(S, sp);
+    most = std::max(most, sp.np);
+  }
+  LoadMem mem;
+  bool room = mem.get(S, load_bytes(g, most));
+  I.g = g;
+  I.ndst = nullptr;
+  room = room && build_tables(S, I) == PIC_OK;
+  for (int s = 0; s < PIC_MAX_SPECIES && room; s++) {
+    Species& sp = I.sp[s];
+    if (keep[s].np == 0) continue;
+    sp.allocs.clear();
+    room = alloc_species(S, I, sp, keep[s].cap, keep[s].desc.chunk) == PIC_OK;
+    sp.np = keep[s].np;
+    sp.desc.qm = keep[s].desc.qm;
+  }
+  if (!room) {
+    (void)hipGetLastError();
+    for (int s = 0; s < PIC_MAX_SPECIES; s++) {
+      if (keep[s].np == 0) continue;
+      Species& sp = I.sp[s];
+      if (sp.allocs != keep[s].allocs)
+        for (void* p : sp.allocs) (void)hipFree(p);
+      sp = keep[s];
+      HIPCHK(S, hipMemcpy(sp.ctl, &ctl[s], sizeof ctl[s], hipMemcpyHostToDevice));
+    }
+    if (I.ndst) (void)hipFree(I.ndst);
+    I.g = g0;
+    I.ndst = ndst0;
+    return PIC_OK;
+  }
+  S.dirty = true;
+  set_current_scale(I);
+  char* const at = mem.at;
+  for (int s = 0; s < PIC_MAX_SPECIES && st == PIC_OK; s++) {
+    Species& sp = I.sp[s];
+    if (keep[s].np == 0) continue;
+    mem.at = at;
+    LoadArgs A = load_args(g, sp.np, 0, mem);
+    load_from(A, keep[s].desc, pic_cur(ctl[s]));
+    LoadStatus ls;
+    st = load_count(S, A, ls);
+    if (st == PIC_OK) st = load_place(S, A, sp, 0, ls);
+    if (st != PIC_OK) break;
+    load_ctl(ctl[s], 0, ls);
+    HIPCHK(S, hipMemcpy(sp.ctl, &ctl[s], sizeof ctl[s], hipMemcpyHostToDevice));
+  }
+  S.ctl_current = false;
+  for (Species& k : keep)
+    for (void* p : k.allocs) (void)hipFree(p);
+  (void)hipFree(ndst0);
+  return st;
+}
+
+// Settle the tiles of every instance that holds particles (see tile_open).
+pic_status settle_tiles(Sim& S) {
+  for (Instance& I : S.inst) {
+    if (I.settled) continue;
+    const int64_t n = instance_particles(I);
+    if (n == 0) continue;
+    if (tile_open(I)) {
+      GridDesc g;
+      pic_status st = setup_grid(S, I.cfg, S.sort_interval, g, (double)n / I.g.ncell);
+      if (st == PIC_OK && !same_tiles(g, I.g)) st = retile(S, I, g);
+      if (st != PIC_OK) return st;
+    }
+    I.settled = true;
+  }
+  return PIC_OK;
 }
 
 // Moving window: grid arrays are kept in ring order along x1 (ring column r
@@ -2286,7 +2438,8 @@ pic_status sim_autotune(Sim& S, pic_tune* io) {
   for (const Instance& I : S.inst)
     if (I.cfg.move_window || I.g.cyl)
       return S.fail(PIC_E_UNSUPPORTED, "the autotuner does not handle a moving window or the r-z geometry");
-  pic_status st = refresh_descriptors(S);
+  pic_status st = settle_tiles(S);
+  if (st == PIC_OK) st = refresh_descriptors(S);
   if (st != PIC_OK) return st;
   if (S.sgroups.empty()) return S.fail(PIC_E_STATE, "autotune needs loaded particles");
   if ((st = sim_sync(S)) != PIC_OK) return st;
