@@ -1520,7 +1520,11 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
       snu[r][1] = uy;
       snu[r][2] = uz;
       // ---- what the deposit needs
-      const bool moved = mv[0] != 0 || mv[1] != 0 || mv[2] != 0 || en[0] != e[0] || en[1] != e[1] || en[2] != e[2];
+      // (ordered comparisons: a particle whose momentum is infinite or not a
+      // number has moves that are not numbers; it adds nothing to the current,
+      // nor to the sums that set the unit of the others)
+      const bool moved = mv[0] != 0 || mv[1] != 0 || mv[2] != 0 || __builtin_islessgreater(en[0], e[0]) ||
+                         __builtin_islessgreater(en[1], e[1]) || __builtin_islessgreater(en[2], e[2]);
       if (moved) {
 #pragma unroll
         for (int d = 0; d < 3; d++) se0[r][d] = e[d];
@@ -1914,12 +1918,16 @@ __device__ void process_item2(const StoreDesc& S, int cur, const Item it, int ii
         sen[r][d] = en[d];
       }
       smv[r] = (mv[0] + 1) | ((mv[1] + 1) << 2);
-      sjc[r] = (jlo[1] + l[1]) * JR[0] + jlo[0] + l[0];
       swq[r] = pw[r];
       sv3[r] = pw[r] * uz * gi;
+      // (a particle whose momentum is infinite or not a number adds nothing to
+      // the current, nor to the sums that set the unit of the others)
+      if (uu2 < INFINITY) {
+        sjc[r] = (jlo[1] + l[1]) * JR[0] + jlo[0] + l[0];
 #pragma unroll
-      for (int d = 0; d < 2; d++) bsum[d] += fabsf(pw[r] * ((float)mv[d] + (en[d] - e[d])));
-      bsum[2] += fabsf(sv3[r]);
+        for (int d = 0; d < 2; d++) bsum[d] += fabsf(pw[r] * ((float)mv[d] + (en[d] - e[d])));
+        bsum[2] += fabsf(sv3[r]);
+      }
     }
     if (count) {
       // wave-aggregated count per rebin slot (almost every particle is in slot 13)
