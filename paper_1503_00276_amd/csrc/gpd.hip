@@ -1208,6 +1208,14 @@ __device__ void process_item(const StoreDesc& S, int cur, int unit, const Item i
 // bits coarser for a thermal plasma, and 0.8 or 1.2 bits more with the
 // quadratic or cubic shape.  A 32-bit tile halves the LDS lane traffic of the
 // adds and drops the sign extension of each one.
+//
+// In a plasma that moves as one the sum is that product, and grows with the
+// tile: in tiles of 256 cells the current of a relativistic drift had an RMS
+// error of 8.2e-8 of its largest value (quadratic, a particle per cell; 3.3e-8 in
+// 64 cells).  There a second bound counts the particles that can reach a node
+// (class_reach): 3.2e-8, and the default tiles stay no coarser than 64 cells
+// were.  96^3 cells, thermal, us a step without and with it: linear at 1 and 4
+// per cell 118 and 122, 192 and 199; quadratic 163 and 168, 297 and 303.
 
 constexpr int kSplitR = 3;  // particles per thread per work item
 
@@ -1230,8 +1238,15 @@ constexpr size_t kInterleaveLds = 64 * sizeof(int) + (size_t)kSplitR * kBlock * 
 //
 // interleave_slots: key[r] is the class of the thread's r-th particle (-1:
 // none); on return pos[r] is its slot in the item.  smem is free LDS of at
-// least kInterleaveLds bytes; every thread of the workgroup calls it.
-__device__ __forceinline__ void interleave_slots(const int (&key)[kSplitR], int (&pos)[kSplitR], float* smem) {
+// least kInterleaveLds bytes; every thread of the workgroup calls it.  With ex
+// > 0 (the tile's extents ex, ey) the second wavefront leaves the class counts'
+// reach in *reach, beside the first one's tables.
+template <int ORDER>
+__device__ __forceinline__ float class_reach(int n, int ex, int ey);
+
+template <int ORDER>
+__device__ __forceinline__ void interleave_slots(const int (&key)[kSplitR], int (&pos)[kSplitR], float* smem, int ex,
+                                                 int ey, float* reach) {
   constexpr int R = kSplitR;
   const int tid = threadIdx.x;
   int* s_n = (int*)smem;                                      // [64]
@@ -1260,11 +1275,63 @@ __device__ __forceinline__ void interleave_slots(const int (&key)[kSplitR], int 
       acc += (int)__popcll(m);
     }
   }
+  if (ORDER <= 2 && ex > 0 && tid >= 64 && tid < 128) {
+    const float top = class_reach<ORDER>(s_n[tid - 64], ex, ey);
+    if (tid == 64) *reach = top;
+  }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < R; r++)
     pos[r] = key[r] >= 0 ? s_l[lev[r]] + (int)__popcll(s_m[lev[r]] & ((1ull << key[r]) - 1ull)) : -1;
   __syncthreads();  // the tables are read before the LDS is reused
+}
+
+// The particles that can reach one node, for the fixed point of tiles of more
+// than 64 cells.  The classes are the columns (x, y) of the tile, or the columns
+// by z modulo 2 or 4, where ex ey divides 64; n is the count of the lane's
+// class (one wavefront calls it).  A particle that ends the step in cell c
+// deposits on nodes c - h + 1 .. c + h of an axis (h = 2 for the linear shape, 3
+// else), so a node of component x1 gets, over the cells of that window, the
+// move times a transverse weight of at most the mean of the old and the new
+// shape at the node: peak, (S(1) + peak) / 2, S(1) / 2 for the cells that touch
+// it, their neighbours and the next (S(1): the shape one cell off; along x3 the
+// peak is taken for all).  Cells are taken modulo the extents, which is how a
+// strayed particle is classed.  Returns the largest weighted count over the
+// nodes, for components x1 and x2; that of x3 is smaller.
+template <int ORDER>
+__device__ __forceinline__ float class_reach(int n, int ex, int ey) {
+  constexpr int H = ORDER == 1 ? 2 : 3;
+  constexpr float peak = shape_peak<ORDER>();
+  constexpr float s1 = ORDER == 1 ? 0.0f : (ORDER == 2 ? 0.125f : 0.16666667f);
+  const int lane = threadIdx.x & 63;
+  for (int off = ex * ey; off < 64; off <<= 1) n += __shfl_xor(n, off);
+  // weight of the cell k cells from the node's own, k = -H .. H - 1
+  auto tau = [&](int k) {
+    const int far = k < 0 ? -k - 1 : k;  // 0, 1, 2
+    return far == 0 ? peak : (far == 1 ? 0.5f * (s1 + peak) : 0.5f * s1);
+  };
+  // sums over the window along an axis of extent e and lane stride st: plain
+  // (each cell once) and weighted
+  auto window = [&](float v, int e, int st, bool weighted) {
+    const int x = (lane / st) & (e - 1);
+    float a = 0.0f;
+    if (!weighted && 2 * H >= e) {
+      a = v;
+      for (int off = st; off < e * st; off <<= 1) a += __shfl_xor(a, off);
+      return a;
+    }
+#pragma unroll
+    for (int k = -H; k < H; k++) {
+      const float o = __shfl(v, lane + (((x + k) & (e - 1)) - x) * st);
+      a += weighted ? tau(k) * o : o;
+    }
+    return a;
+  };
+  const float c = (float)n;
+  float top = fmaxf(window(window(c, ex, 1, false), ey, ex, true), window(window(c, ex, 1, true), ey, ex, false));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+  return top * peak;
 }
 
 // FIXED: the LDS strides are the 12-node rows and 144-node planes that 4x4xN
@@ -1274,6 +1341,7 @@ template <int ORDER, bool FIXED, typename Acc>
 __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii, int jp, int kstep, bool count, float* smem,
                               int* scnt, float* sred) {
   constexpr bool kWide = sizeof(Acc) == 8;
+  constexpr bool kColumns = !kWide && !FIXED && ORDER <= 2;  // a second bound for the unit (see below)
   constexpr int NG = ORDER + 1;  // gather taps per axis
   constexpr int K = ORDER + 1;   // deposit core per axis
   constexpr int W = ORDER + 2;   // deposit window per axis
@@ -1548,24 +1616,46 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
       }
     }
   }
+  // Tiles of more cells: the item's largest |w| |move| dx/dt, for a second bound.
+  // (The default tiles of the cubic shape and the 4x4xN ones need none.)
+  constexpr float peak2 = shape_peak<ORDER>() * shape_peak<ORDER>();
+  const int column = ext[0] * ext[1];
+  const bool columns = kColumns && column <= 64 && (column & (column - 1)) == 0 && (float)(column * ext[2]) * peak2 > 64.0f;
+  if (columns) {
+    float bm = 0.0f;
+#pragma unroll
+    for (int r = 0; r < R; r++)
+#pragma unroll
+      for (int d = 0; d < 3; d++)
+        if (sjc[r] >= 0)
+          bm = fmaxf(bm, g.cdt[d] * fabsf(swq[r] * ((float)(((smv[r] >> (2 * d)) & 3) - 1) + (sen[r][d] - se0[r][d]))));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) bm = fmaxf(bm, __shfl_xor(bm, off));
+    if ((tid & 63) == 0) sred[3 * (kBlock / 64) + (tid >> 6)] = bm;
+  }
   block_partial<3>(bsum, sred);
   const int any_strayed = __syncthreads_or(strayed ? 1 : 0);  // also: phase A done, fields dead
   const int any_bad = __syncthreads_or(bad ? 1 : 0);
   float btop = 0.0f;
 #pragma unroll
   for (int d = 0; d < 3; d++) btop = fmaxf(btop, g.cdt[d] * block_total<3>(sred, d));
-  btop *= shape_peak<ORDER>() * shape_peak<ORDER>();
-  // (the int64 mode: the instance's own fixed point, as in the one-phase kernel)
-  int eg = 0;
-  (void)frexpf(g.jscale, &eg);  // jscale = 2^(eg-1)
-  const int e_item = __builtin_amdgcn_readfirstlane(kWide ? eg - 1 : item_exponent32(btop));
-  const float Q = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, e_item))));
+  btop *= peak2;
+  // A plasma that moves as one sums to more than the particles of 64 cells at
+  // the largest |w| |move| would: then the second bound is that largest times
+  // the particles that can reach a node (class_reach).
+  float bmax = 0.0f;
+  bool coherent = false;
+  if (columns) {
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; w++) bmax = fmaxf(bmax, sred[3 * (kBlock / 64) + w]);
+    coherent = btop * (float)(column * ext[2]) > 64.0f * bmax * (float)(it.end - it.begin);
+  }
 
   // 3. store the new state at the item's interleaved slots (the LDS of the
   // staged fields is free), then clear the current tile over it
   {
     int pos[R];
-    interleave_slots(skey, pos, smem);
+    interleave_slots<ORDER>(skey, pos, smem, coherent ? ext[0] : 0, ext[1], &sred[4 * (kBlock / 64)]);
 #pragma unroll
     for (int r = 0; r < R; r++) {
       if (pos[r] < 0) continue;
@@ -1581,6 +1671,12 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
       idp[q] = pid[r];
     }
   }
+  if (coherent) btop = fminf(btop, bmax * sred[4 * (kBlock / 64)]);
+  // (the int64 mode: the instance's own fixed point, as in the one-phase kernel)
+  int eg = 0;
+  (void)frexpf(g.jscale, &eg);  // jscale = 2^(eg-1)
+  const int e_item = __builtin_amdgcn_readfirstlane(kWide ? eg - 1 : item_exponent32(btop));
+  const float Q = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, e_item))));
   for (int idx = tid; idx < 3 * jpl; idx += nthr) sJ[idx] = (Acc)0;
   if (tid == 0) {
     if (any_strayed) S.ctl->flag = 1;
@@ -2086,7 +2182,7 @@ __device__ __forceinline__ void gpd_body(const StoreDesc* __restrict__ stores, i
   __shared__ int s_pref[kMaxGroup + 1];
   __shared__ int s_cur[kMaxGroup];
   __shared__ int s_cnt[PIC_NSLOT];
-  __shared__ float s_red[3 * (kBlock / 64)];
+  __shared__ float s_red[4 * (kBlock / 64) + 1];
   // per store its buffer set (bit 0) and, for the one-phase Cartesian kernels,
   // the biased exponent of its unit of this step (above it); the first wave
   // counts the items, the others take the units, so their loads overlap

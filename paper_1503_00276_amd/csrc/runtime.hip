@@ -200,11 +200,13 @@ bool two_phase2(const pic_config& c) {
 // fields with a halo and folds its current, so tiles are large where there
 // are items enough to fill the chip, and small where there are not.
 //   3D, two-phase kernel: 512 particles per tile, from 64 to 256 cells (ppc is
-//     the mean particles per cell of what is loaded; 0 before, see tile_open).  96^3
-//     cells, us a step with 4x4x4 / 8x4x4 / 8x8x4 tiles: quadratic shape at
+//     the mean particles per cell of what is loaded; 0 before, see tile_open).
+//     96^3 cells, us a step with 4x4x4 / 8x4x4 / 8x8x4 tiles: quadratic shape at
 //     1, 2, 4, 8 per cell 295 / 219 / 175, 313 / 242 / 223, 363 / 319 / 350,
 //     522 / 572 / 572; cubic 375 / 267 / 249, 405 / 319 / 330, 483 / 457 / 548,
-//     733 / 837 / 958; linear 222 / 157 / 131 ... 375 / 389 / 387.
+//     733 / 837 / 958; linear 222 / 157 / 131 ... 375 / 389 / 387.  The cubic shape
+//     takes at most 128 cells: there the unit of its current needs no second
+//     bound (class_reach in gpd.hip), whose registers cost every cubic box 2.7 %.
 //   2D, two-phase kernel: 1,024 tiles (one wave of workgroups), from 64 to 256
 //     cells: 64x64 8x8 16.7 us, 16x16 17.9; 512x256 at 4 per cell 16x8 32, 16x16
 //     38; 1024x512 at 8 per cell 16x8 155, 16x16 144, 32x16 140; a batch of 24
@@ -213,7 +215,7 @@ bool two_phase2(const pic_config& c) {
 //   3D, one-phase kernel: 512 cells.
 // total: cells of all instances, which fill the chip together.
 double default_tile_cells(const GridDesc& g, int64_t total, double ppc) {
-  if (pic_gpd_split(g)) return ppc > 0.0 ? std::min(256.0, std::max(64.0, 512.0 / ppc)) : 64.0;
+  if (pic_gpd_split(g)) return ppc > 0.0 ? std::min(g.order == 3 ? 128.0 : 256.0, std::max(64.0, 512.0 / ppc)) : 64.0;
   if (g.dim == 3) return 512.0;
   if (pic_gpd_two_phase2(g)) return std::min(256.0, std::max(64.0, (double)total / 1024.0));
   return std::min(256.0, std::max(128.0, (double)total / 512.0));
