@@ -56,20 +56,14 @@ constexpr int kRhoPer = 4;  // particles per thread and pass over a tile
 // particle's (ORDER+1)^DIM contributions to the global array with FP64 atomics
 // cost 26.5 ms for 16.8 M particles of a cubic shape (64 each, 40 G adds/s);
 // this kernel adds about three sums per particle there and takes 0.72 ms.
-//
-// The LDS sums are integers (LDS integer adds run several times faster than
-// floating ones, and their sum does not depend on the order): a pass takes at
-// most kRhoPer * kBlock = 1024 particles, whose largest |w| lies below 2^k;
-// their weights are scaled by 2^(51-k), so a contribution is at most 2^51 and
-// adding 1.5 * 2^52 to it leaves the nearest integer in the low bits of the
-// sum.  The rounding is 2^-52 of the pass's largest weight, that of an FP64
-// add to a node holding one such particle, and 1024 of them stay below 2^62.
+// The LDS sums are FP64 too, so a node reached by light particles only keeps its
+// relative precision beside heavy ones.  (64-bit integer sums in units of the
+// heaviest particle took 0.56 ms there, 143 against 178 us for 7.1 M of a
+// quadratic shape, 74 against 71 for a linear one.)
 template <int DIM, int ORDER>
 __global__ void __launch_bounds__(kBlock) rho64(const StoreDesc* __restrict__ sp, double* rho, int kstep, int par) {
-  extern __shared__ unsigned long long sR[];
-  __shared__ float s_w[kBlock / 64];
+  extern __shared__ double sR[];
   constexpr int NO = ORDER + 1;
-  constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52
   const StoreDesc& S = *sp;
   const GridDesc& g = S.g;
   const int cur = pic_cur(*S.ctl);
@@ -93,7 +87,6 @@ __global__ void __launch_bounds__(kBlock) rho64(const StoreDesc* __restrict__ sp
     for (int begin = it.begin; begin < it.end; begin += kRhoPer * kBlock) {
       int cell[kRhoPer];
       float w[kRhoPer], e[kRhoPer][DIM];
-      float wm = 0.0f;
 #pragma unroll
       for (int r = 0; r < kRhoPer; r++) {
         const int p = begin + r * kBlock + tid;
@@ -105,18 +98,9 @@ __global__ void __launch_bounds__(kBlock) rho64(const StoreDesc* __restrict__ sp
 #pragma unroll
           for (int d = 0; d < DIM; d++) e[r][d] = S.eps[cur][d][p];
         }
-        wm = fmaxf(wm, fabsf(w[r]));
       }
-      for (int q = tid; q < rn; q += kBlock) sR[q] = 0ull;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) wm = fmaxf(wm, __shfl_xor(wm, off));
-      if ((tid & 63) == 0) s_w[tid >> 6] = wm;
+      for (int q = tid; q < rn; q += kBlock) sR[q] = 0.0;
       __syncthreads();
-#pragma unroll
-      for (int k = 0; k < kBlock / 64; k++) wm = fmaxf(wm, s_w[k]);
-      int ex = 0;
-      (void)frexpf(wm, &ex);  // wm < 2^ex
-      const double Q = ldexp(1.0, 51 - ex);
 #pragma unroll
       for (int r = 0; r < kRhoPer; r++) {
         if (cell[r] < 0) continue;
@@ -139,28 +123,25 @@ __global__ void __launch_bounds__(kBlock) rho64(const StoreDesc* __restrict__ sp
           for (int i = 0; i < NO; i++)
             if ((unsigned)(wc + b + i) >= (unsigned)g.nx[0]) wt[0][i] = 0.0;
         }
-        const double q = (double)w[r] * Q;
-        unsigned long long* base = sR + at[0] + R[0] * (at[1] + R[1] * at[2]);
+        const double q = (double)w[r];
+        double* base = sR + at[0] + R[0] * (at[1] + R[1] * at[2]);
 #pragma unroll
         for (int k = 0; k < (DIM == 3 ? NO : 1); k++) {
           const double qz = DIM == 3 ? q * wt[2][k] : q;
 #pragma unroll
           for (int j = 0; j < NO; j++) {
             const double qy = qz * wt[1][j];
-            unsigned long long* row = base + R[0] * (j + R[1] * k);
+            double* row = base + R[0] * (j + R[1] * k);
 #pragma unroll
-            for (int i = 0; i < NO; i++) {
-              const long long v = __double_as_longlong(fma(qy, wt[0][i], kMagic)) - __double_as_longlong(kMagic);
-              __hip_atomic_fetch_add(row + i, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
+            for (int i = 0; i < NO; i++)
+              __hip_atomic_fetch_add(row + i, qy * wt[0][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
         }
       }
       __syncthreads();
-      const double unit = ldexp(1.0, ex - 51);
       for (int n = tid; n < rn; n += kBlock) {
-        const long long v = (long long)sR[n];
-        if (v == 0) continue;
+        const double v = sR[n];
+        if (v == 0.0) continue;
         const int x = n % R[0], y = (n / R[0]) % R[1], z = DIM == 3 ? n / (R[0] * R[1]) : 0;
         const int gx = pic_wrap(org[0] - sl[0] - lo + x, g.nx[0]);
         int gy = org[1] - sl[1] - lo + y;
@@ -173,7 +154,7 @@ __global__ void __launch_bounds__(kBlock) rho64(const StoreDesc* __restrict__ sp
           gy = pic_wrap(gy, g.nx[1]);
         }
         const int gz = DIM == 3 ? pic_wrap(org[2] - sl[2] - lo + z, g.nx[2]) : 0;
-        unsafeAtomicAdd(rho + gx + (size_t)g.nx[0] * (gy + (size_t)g.nx[1] * gz), (double)v * unit);
+        unsafeAtomicAdd(rho + gx + (size_t)g.nx[0] * (gy + (size_t)g.nx[1] * gz), v);
       }
       __syncthreads();
     }
