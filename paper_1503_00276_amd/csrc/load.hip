@@ -69,18 +69,6 @@ __device__ __forceinline__ bool load_convert(const LoadArgs& A, long long q, int
   return true;
 }
 
-// Index of a cell in tile order: its tile times the tile's volume plus its
-// place in the tile, x fastest.
-__device__ __forceinline__ int load_key(const GridDesc& g, const int c[3]) {
-  int t[3] = {0, 0, 0}, l[3] = {0, 0, 0};
-  for (int d = 0; d < g.dim; d++) {
-    t[d] = c[d] / g.tile[d];
-    l[d] = c[d] - t[d] * g.tile[d];
-  }
-  return pic_tile_index(g, t[0], t[1], t[2]) * (g.tile[0] * g.tile[1] * g.tile[2]) + l[0] +
-         g.tile[0] * (l[1] + g.tile[1] * l[2]);
-}
-
 __device__ __forceinline__ bool finite64(double v) { return fabs(v) <= 1.7976931348623157e308; }
 
 __global__ void __launch_bounds__(kBlock) load_count(const LoadArgs A) {
@@ -120,7 +108,7 @@ __global__ void __launch_bounds__(kBlock) load_count(const LoadArgs A) {
       }
     }
     um = fmax(um, (double)u[0] * u[0] + (double)u[1] * u[1] + (double)u[2] * u[2]);
-    A.rank[p] = atomicAdd(&A.cells[load_key(g, c)], 1);
+    A.rank[p] = atomicAdd(&A.cells[pic_load_key(g, c)], 1);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -289,7 +277,7 @@ __global__ void __launch_bounds__(kBlock) load_place(const LoadArgs A, const Sto
       w = (float)A.w[q];
       id = (int)(A.id0 + q);
     }
-    const int pos = A.slot[A.cells[load_key(g, c)] + A.rank[p]];
+    const int pos = A.slot[A.cells[pic_load_key(g, c)] + A.rank[p]];
     S.cell[set][pos] = cell;
     for (int d = 0; d < g.dim; d++) S.eps[set][d][pos] = e[d];
     for (int k = 0; k < 3; k++) S.u[set][k][pos] = u[k];

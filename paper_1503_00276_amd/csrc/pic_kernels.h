@@ -89,6 +89,18 @@ struct LoadArgs {
   int *rank, *slot;          // [old + n]
   LoadStatus* status;        // zeroed but first = ~0 and idmax = -1
 };
+// Index of a cell in tile order: its tile times the tile's volume plus its place
+// in the tile, x fastest.  (Ragged tiles count in full: a box of nearly 2^31
+// cells can have more than 2^31 of these.)
+__host__ __device__ inline long long pic_load_key(const GridDesc& g, const int c[3]) {
+  int t[3] = {0, 0, 0}, l[3] = {0, 0, 0};
+  for (int d = 0; d < g.dim; d++) {
+    t[d] = c[d] / g.tile[d];
+    l[d] = c[d] - t[d] * g.tile[d];
+  }
+  return (long long)pic_tile_index(g, t[0], t[1], t[2]) * (g.tile[0] * g.tile[1] * g.tile[2]) + l[0] +
+         g.tile[0] * (l[1] + g.tile[1] * l[2]);
+}
 hipError_t pic_launch_load_count(const LoadArgs& a, hipStream_t st);
 hipError_t pic_launch_load_place(const LoadArgs& a, const StoreDesc& s, int set, hipStream_t st);
 hipError_t pic_launch_neighbour_table(const GridDesc& g, int* ndst, hipStream_t st);

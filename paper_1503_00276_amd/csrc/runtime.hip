@@ -1235,6 +1235,7 @@ struct LoadMem {
   }
 };
 
+// Keys of a load (pic_load_key).
 size_t load_keys(const GridDesc& g) { return (size_t)g.ntiles * g.tile[0] * g.tile[1] * g.tile[2]; }
 
 // What load_args takes for a store of 'total' particles.
