@@ -1351,9 +1351,9 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
   A.w = in[2];
   StoreCtl c{};
   int set = 0;
-  if (old > 0) {
+  if (sp.used && sp.ctl) {  // (also an emptied store keeps its counters)
     c = host_ctl(S, sp);
-    load_from(A, sp.desc, pic_cur(c));
+    if (old > 0) load_from(A, sp.desc, pic_cur(c));
     set = 1 - pic_cur(c);  // (the set read from stays as it is)
   }
   LoadStatus ls;
