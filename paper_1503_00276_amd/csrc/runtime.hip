@@ -2238,7 +2238,8 @@ pic_status sim_info(const Sim& S, int i, pic_info* out) {
 // ---------------------------------------------------------------------------
 
 // Launch layout of a whole Sim: a particles-per-tile target (0 = keep the
-// tiles in use), the sort interval and the chunk.
+// tiles in use), the sort interval and the chunk (0 = each store keeps its own:
+// the default chunks follow the particles loaded).
 struct Layout {
   int ppt = 0, aspect = 2, si = 1, chunk = 2048;
 };
@@ -2246,6 +2247,7 @@ struct Layout {
 // The state an autotune restores before every candidate and at the end.
 struct Snapshot {
   std::vector<std::vector<HostParticles>> parts;  // [instance][species]
+  std::vector<std::vector<int>> chunk;             // of the stores, likewise (0: not in use)
   std::vector<float*> F, Jout;                     // device copies
   int64_t steps = 0;
   ~Snapshot() {
@@ -2312,7 +2314,7 @@ pic_status layout_configs(Sim& S, const Layout& L, std::vector<pic_config>& out)
     const Instance& I = S.inst[i];
     pic_config c = I.cfg;
     c.sort_interval = L.si;
-    c.chunk = L.chunk;
+    if (L.chunk > 0) c.chunk = L.chunk;
     for (int d = 0; d < 3; d++) c.tile[d] = d < c.ndim ? I.g.tile[d] : 0;
     if (L.ppt > 0) {
       pic_config probe = c;
@@ -2336,7 +2338,12 @@ pic_status layout_configs(Sim& S, const Layout& L, std::vector<pic_config>& out)
 
 // Install a layout and reload the snapshot into it (host binning of all
 // instances and species in parallel, then the uploads).
-pic_status apply_layout(Sim& S, const std::vector<pic_config>& cfgs, int si, const Snapshot& snap) {
+pic_status apply_layout(Sim& S, const std::vector<pic_config>& cfgs, const Layout& L, const Snapshot& snap) {
+  const int si = L.si;
+  auto chunk = [&](int i, int s) {
+    const int own = snap.chunk[i][s];
+    return L.chunk > 0 ? L.chunk : (own > 0 ? own : 2048);  // (2048: a store without particles)
+  };
   HIPCHK(S, hipStreamSynchronize(S.stream));
   pic_status st;
   const int ni = (int)S.inst.size();
@@ -2346,12 +2353,14 @@ pic_status apply_layout(Sim& S, const std::vector<pic_config>& cfgs, int si, con
   std::vector<Binned> bins((size_t)ni * PIC_MAX_SPECIES);
   parallel_for(ni * PIC_MAX_SPECIES, [&](int k) {
     const int i = k / PIC_MAX_SPECIES, s = k % PIC_MAX_SPECIES;
-    if (S.inst[i].sp[s].used) bin_particles(gs[i], store_chunk(gs[i], cfgs[i].chunk), snap.parts[i][s], bins[k]);
+    if (S.inst[i].sp[s].used) bin_particles(gs[i], store_chunk(gs[i], chunk(i, s)), snap.parts[i][s], bins[k]);
   });
   for (int i = 0; i < ni; i++) {
     Instance& I = S.inst[i];
     I.cfg.sort_interval = cfgs[i].sort_interval;
-    I.cfg.chunk = cfgs[i].chunk;
+    // (what a store that grows later is made with)
+    for (int s = PIC_MAX_SPECIES - 1; s >= 0; s--)
+      if (snap.chunk[i][s] > 0 || L.chunk > 0) I.cfg.chunk = chunk(i, s);
     for (int d = 0; d < 3; d++) I.cfg.tile[d] = cfgs[i].tile[d];
     I.g = gs[i];
     if ((st = build_tables(S, I)) != PIC_OK) return st;
@@ -2359,7 +2368,7 @@ pic_status apply_layout(Sim& S, const std::vector<pic_config>& cfgs, int si, con
       Species& sp = I.sp[s];
       if (!sp.used) continue;
       int64_t cap = std::max<int64_t>(sp.cap, 1);
-      if ((st = alloc_species(S, I, sp, cap, cfgs[i].chunk)) != PIC_OK) return st;
+      if ((st = alloc_species(S, I, sp, cap, chunk(i, s))) != PIC_OK) return st;
       sp.desc.qm = (float)(1.0 / sp.rqm);
     }
     set_current_scale(I);
@@ -2471,11 +2480,16 @@ pic_status sim_autotune(Sim& S, pic_tune* io) {
   Snapshot snap;
   snap.steps = S.steps;
   snap.parts.resize(S.inst.size());
+  snap.chunk.resize(S.inst.size());
   for (size_t i = 0; i < S.inst.size(); i++) {
     Instance& I = S.inst[i];
     snap.parts[i].resize(PIC_MAX_SPECIES);
+    snap.chunk[i].assign(PIC_MAX_SPECIES, 0);
     for (int s = 0; s < PIC_MAX_SPECIES; s++)
-      if (I.sp[s].used && (st = read_back(S, I.sp[s], I.g.dim, snap.parts[i][s])) != PIC_OK) return st;
+      if (I.sp[s].used) {
+        if ((st = read_back(S, I.sp[s], I.g.dim, snap.parts[i][s])) != PIC_OK) return st;
+        snap.chunk[i][s] = I.sp[s].desc.chunk;
+      }
     const size_t nc = (size_t)I.g.ncell;
     float *f = nullptr, *j = nullptr;
     HIPCHK(S, hipMalloc(&f, 6 * nc * sizeof(float)));
@@ -2487,12 +2501,16 @@ pic_status sim_autotune(Sim& S, pic_tune* io) {
   }
   Layout start;
   start.si = S.sort_interval;
-  start.chunk = 2048;
-  for (const Species& sp : S.inst[0].sp)
-    if (sp.used) {
-      start.chunk = sp.desc.chunk;
-      break;
-    }
+  // one chunk if all stores have the same, else each keeps its own
+  int own = 0;  // the first store's
+  start.chunk = -1;
+  for (const auto& v : snap.chunk)
+    for (int c : v)
+      if (c > 0) {
+        if (own == 0) own = c;
+        start.chunk = start.chunk < 0 || start.chunk == c ? c : 0;
+      }
+  start.chunk = std::max(start.chunk, 0);
   std::vector<pic_config> start_cfgs;
   if ((st = layout_configs(S, start, start_cfgs)) != PIC_OK) return st;
   // every layout tried, by its resolved per-instance tiles, interval and chunk
@@ -2507,13 +2525,13 @@ pic_status sim_autotune(Sim& S, pic_tune* io) {
   double best_ms = 0.0;
   int tried = 0;
   auto trial = [&](const Layout& L, const std::vector<pic_config>& c, double* ms) -> pic_status {
-    pic_status r = apply_layout(S, c, L.si, snap);
+    pic_status r = apply_layout(S, c, L, snap);
     if (r == PIC_OK) r = time_layout(S, io->trial_steps, every, ms);
     tried++;
     return r;
   };
   if ((st = trial(start, start_cfgs, &best_ms)) != PIC_OK) {
-    (void)apply_layout(S, start_cfgs, start.si, snap);
+    (void)apply_layout(S, start_cfgs, start, snap);
     return st;
   }
   seen.push_back(key(start_cfgs, start.si, start.chunk));
@@ -2607,17 +2625,17 @@ pic_status sim_autotune(Sim& S, pic_tune* io) {
   }
   if (st != PIC_OK) {
     std::string why = S.err;
-    (void)apply_layout(S, start_cfgs, start.si, snap);
+    (void)apply_layout(S, start_cfgs, start, snap);
     S.profiling = was_profiling;
     S.err = why;
     return st;
   }
-  if ((st = apply_layout(S, best_cfgs, best.si, snap)) != PIC_OK) return st;
+  if ((st = apply_layout(S, best_cfgs, best, snap)) != PIC_OK) return st;
   S.profiling = was_profiling;
   io->candidates = tried;
   io->particles_per_tile = best.ppt;
   io->sort_interval = best.si;
-  io->chunk = best.chunk;
+  io->chunk = best.chunk > 0 ? best.chunk : own;
   io->ms_before = ms_before;
   io->ms_after = best_ms;
   return PIC_OK;
