@@ -479,6 +479,13 @@ int default_chunk(const Sim& S, const pic_config& c, const GridDesc& g, int64_t 
   return all < (1 << 18) ? 256 : split(2048, 512, 2048);
 }
 
+// The default chunk of a store that took more particles where they are: larger
+// chunks make fewer items, so the item arrays hold them.
+void grow_chunk(const Sim& S, const Instance& I, Species& sp, int64_t want) {
+  if (I.cfg.chunk > 0) return;
+  sp.desc.chunk = std::max(sp.desc.chunk, store_chunk(I.g, default_chunk(S, I.cfg, I.g, want)));
+}
+
 // Bytes rounded up to a multiple of 256 (sub-buffers of an allocation).
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -1389,6 +1396,8 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
     sp.desc.qm = (float)(1.0 / rqm);
     set = 0;
     c = StoreCtl{};
+  } else {
+    grow_chunk(S, I, sp, want);
   }
   settle_species(I, species, wm);
   st = load_place(S, A, sp, set, ls);
@@ -1508,6 +1517,8 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
     sp.used = true;
     sp.rqm = rqm;
     sp.desc.qm = (float)(1.0 / rqm);
+  } else {
+    grow_chunk(S, I, sp, want);
   }
   settle_species(I, species, wm);
   if (win) {
