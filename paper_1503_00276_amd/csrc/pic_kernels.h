@@ -121,8 +121,9 @@ hipError_t pic_launch_charge64(const InstDesc* d_inst, const double* rho0, const
 int pic_reduce_blocks();
 hipError_t pic_launch_field_sums(const InstDesc* d_inst, int ncell, int fpar, double* scratch, double* out,
                                  hipStream_t st);
-hipError_t pic_launch_particle_sums(const StoreDesc* d_store, int np, double rqm, double* scratch,
-                                    double* out, hipStream_t st);
+// exact: independent of the particles' storage order
+hipError_t pic_launch_particle_sums(const StoreDesc* d_store, double rqm, bool exact, double* scratch, double* out,
+                                    hipStream_t st);
 hipError_t pic_launch_sq_sums(const double* v, int n, double* scratch, double* out, hipStream_t st);
 // xmin, dx (3 each): positions scaled to the caller's (null with ids: cell units)
 hipError_t pic_launch_export_state(const StoreDesc* d_store, int np, double* out, int* ids, const double* xmin,

@@ -1815,8 +1815,8 @@ pic_status sim_diag(Sim& S, int i, pic_diag_kind kind, void* out, size_t out_byt
         Species& sp = I.sp[s];
         if (!sp.used || sp.np == 0) continue;
         int k = store_desc_index(S, i, s);
-        HIPCHK(S, pic_launch_particle_sums(S.d_stores + k, (int)sp.np, sp.rqm, S.d_scratch, S.d_out + 2 + 4 * nsp,
-                                           S.stream));
+        HIPCHK(S, pic_launch_particle_sums(S.d_stores + k, sp.rqm, g.acc_mode == PIC_ACC_FIXED64, S.d_scratch,
+                                           S.d_out + 2 + 4 * nsp, S.stream));
         nsp++;
       }
       HIPCHK(S, hipMemcpyAsync(sums, S.d_out, (size_t)(2 + 4 * nsp) * sizeof(double), hipMemcpyDeviceToHost, S.stream));
