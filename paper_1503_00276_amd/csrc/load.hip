@@ -198,18 +198,26 @@ __global__ void __launch_bounds__(kPlanBlock) load_plan(const LoadArgs A, const 
 // for each different count, however many particles a cell has.  (A round per
 // rank, and no interleaving past the 512th, left a 64x64 box at 2,000 per cell
 // with wavefronts in one cell: 197 us a step, linear, 280 quadratic.)
+// A round is a chain of a few LDS reads, shuffles and one barrier; the cells that
+// have its ranks write them themselves where there are few, and are listed for
+// the whole workgroup where there are many.
+constexpr int kSlotBytes = 2 * sizeof(int) + sizeof(unsigned short);  // LDS per cell of a tile
+
 __global__ void __launch_bounds__(kBlock) load_slots(const LoadArgs A, const int* __restrict__ toff) {
   extern __shared__ int lds[];
-  __shared__ int s_min[kBlock / 64];
+  constexpr int W = kBlock / 64;
+  __shared__ int s_n[2][W], s_top[2][W];
   const int vol = A.g.tile[0] * A.g.tile[1] * A.g.tile[2];
-  int* cnt = lds;        // particles of each cell
-  int* act = lds + vol;  // the cells that have the round's ranks, in cell order
-  const int tid = threadIdx.x;
+  int* cnt = lds;                                          // particles of each cell
+  int* first = lds + vol;                                  // its first place in the (cell, rank) list
+  unsigned short* act = (unsigned short*)(lds + 2 * vol);  // the cells that have the round's ranks
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  // each wavefront looks at a run of the cells
+  const int per = (vol + kBlock - 1) / kBlock * 64, k0 = wave * per, k1 = min(vol, k0 + per);
   for (int t = blockIdx.x; t < A.g.ntiles; t += gridDim.x) {
     int* cells = A.cells + (size_t)t * vol;
-    const int start = toff[t];
-    // counts to LDS, and each cell's first place in the (cell, rank) list
-    int run = start;
+    int run = toff[t], at = run;  // at: places given out
     for (int base = 0; base < vol; base += kBlock) {
       const int k = base + tid;
       const int c = k < vol ? cells[k] : 0;
@@ -217,40 +225,55 @@ __global__ void __launch_bounds__(kBlock) load_slots(const LoadArgs A, const int
       block_scan2<kBlock>(c, 0, ea, eb, ta, tb);
       if (k < vol) {
         cnt[k] = c;
-        cells[k] = run + ea;
+        first[k] = cells[k] = run + ea;
       }
       run += ta;
     }
-    int at = start;  // places given out
-    for (int r = 0;;) {
-      int na = 0, top = INT_MAX;  // top: the smallest count above r
-      for (int base = 0; base < vol; base += kBlock) {
-        const int k = base + tid;
-        const int c = k < vol ? cnt[k] : 0;
-        int ea, eb, ta, tb;
-        block_scan2<kBlock>(c > r ? 1 : 0, 0, ea, eb, ta, tb);
-        if (c > r) {
-          act[na + ea] = k;
-          top = min(top, c);
-        }
-        na += ta;
+    __syncthreads();
+    for (int r = 0, par = 0;; par ^= 1) {
+      int n = 0, top = INT_MAX;  // the cells of more than r, and the smallest count of them
+      for (int k = k0; k < k1; k += 64) {
+        const int c = k + lane < k1 ? cnt[k + lane] : 0;
+        n += (int)__popcll(__ballot(c > r));
+        if (c > r) top = min(top, c);
       }
-      if (na == 0) break;  // (the same in every thread)
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) top = min(top, __shfl_xor(top, off));
-      if ((tid & 63) == 0) s_min[tid >> 6] = top;
-      __syncthreads();
+      if (lane == 0) {
+        s_n[par][wave] = n;
+        s_top[par][wave] = top;
+      }
+      __syncthreads();  // (the other parity's entries may still be read)
+      int na = 0, j0 = 0;
 #pragma unroll
-      for (int w = 0; w < kBlock / 64; w++) top = min(top, s_min[w]);
-      // consecutive threads take consecutive ranks of a cell, which lie together
+      for (int w = 0; w < W; w++) {
+        if (w < wave) j0 += s_n[par][w];
+        na += s_n[par][w];
+        top = min(top, s_top[par][w]);
+      }
+      if (na == 0) break;  // (the same in every thread)
       const int ranks = top - r;
-      for (int p = tid; p < na * ranks; p += kBlock) {
-        const int j = p / ranks, q = p - j * ranks;
-        A.slot[cells[act[j]] + r + q] = at + q * na + j;
+      const bool list = ranks > 4;
+      for (int k = k0; k < k1; k += 64) {
+        const bool has = k + lane < k1 && cnt[k + lane] > r;
+        const unsigned long long m = __ballot(has);
+        const int j = j0 + (int)__popcll(m & lt);
+        if (has && list) act[j] = (unsigned short)(k + lane);
+        if (has && !list)
+          for (int q = 0; q < ranks; q++) A.slot[first[k + lane] + r + q] = at + q * na + j;
+        j0 += (int)__popcll(m);
+      }
+      if (list) {
+        __syncthreads();
+        // consecutive threads take consecutive ranks of a cell, which lie together
+        for (int p = tid; p < na * ranks; p += kBlock) {
+          const int j = p / ranks, q = p - j * ranks;
+          A.slot[first[act[j]] + r + q] = at + q * na + j;
+        }
+        __syncthreads();  // the list is read before another round writes it
       }
       at += na * ranks;
       r = top;
-      __syncthreads();  // the cells and the minimum are read before the next round's are written
     }
     __syncthreads();  // the counts are read before the next tile's are written
   }
@@ -313,7 +336,7 @@ hipError_t pic_launch_load_place(const LoadArgs& a, const StoreDesc& s, int set,
   const int vol = a.g.tile[0] * a.g.tile[1] * a.g.tile[2];
   hipLaunchKernelGGL(load_sums, dim3(grid_of(a.g.ntiles, kBlock / 64)), dim3(kBlock), 0, st, a);
   hipLaunchKernelGGL(load_plan, dim3(1), dim3(kPlanBlock), 0, st, a, s, set);
-  hipLaunchKernelGGL(load_slots, dim3(grid_of(a.g.ntiles, 1)), dim3(kBlock), 2 * vol * sizeof(int), st, a,
+  hipLaunchKernelGGL(load_slots, dim3(grid_of(a.g.ntiles, 1)), dim3(kBlock), vol * kSlotBytes, st, a,
                      s.toff[set]);
   hipLaunchKernelGGL(load_place, dim3(grid_of(a.old + a.n, kBlock)), dim3(kBlock), 0, st, a, s, set);
   return hipGetLastError();
