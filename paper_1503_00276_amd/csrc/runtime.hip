@@ -61,6 +61,7 @@ struct Instance {
   double* rho_snap = nullptr;
   bool have_snap = false;
   bool settled = false;  // a step has run with particles: the default tile stays
+  int64_t tiled_for = -1;  // particles the default tile was last chosen by
   Species sp[PIC_MAX_SPECIES];
   int64_t steps = 0;
 };
@@ -1166,9 +1167,11 @@ bool same_tiles(const GridDesc& a, const GridDesc& b) {
   return a.tile[0] == b.tile[0] && a.tile[1] == b.tile[1] && a.tile[2] == b.tile[2];
 }
 
-// Put the tiles of g in force in an instance without particles, once a load has
-// passed its checks; its stores, if any, are allocated anew.
-pic_status take_tiles(Sim& S, Instance& I, const GridDesc& g) {
+// Put the tiles of g, chosen by n particles, in force in an instance without
+// particles, once a load has passed its checks; its stores, if any, are allocated
+// anew.
+pic_status take_tiles(Sim& S, Instance& I, const GridDesc& g, int64_t n) {
+  if (tile_open(I) && instance_particles(I) == 0) I.tiled_for = n;
   if (same_tiles(g, I.g)) return I.ndst ? PIC_OK : build_tables(S, I);
   for (Species& sp : I.sp)
     if (sp.used) free_species(sp);
@@ -1322,6 +1325,9 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
   if (win && species != 0 && !I.sp[0].used) return PIC_OK;
   GridDesc g;
   if (tiles_for(S, I, n, g) != PIC_OK) return PIC_OK;
+  // (the table of tiles that stay needs no checks of the input, and is made
+  // before its kernels are queued)
+  if (!I.ndst && same_tiles(g, I.g) && build_tables(S, I) != PIC_OK) return PIC_OK;
   WinCtl wc;
   pic_status st = read_win(S, I, wc);
   if (st != PIC_OK) return st;
@@ -1375,7 +1381,7 @@ pic_status load_device(Sim& S, Instance& I, int species, double rqm, int64_t n, 
                           : S.fail(PIC_E_RANGE, "particle outside the moving window");
   double wm;
   memcpy(&wm, &ls.w, 8);
-  if ((st = take_tiles(S, I, g)) != PIC_OK) return st;
+  if ((st = take_tiles(S, I, g, n)) != PIC_OK) return st;
   const int64_t want = wanted_capacity(I, species, total);
   Species keep;  // the arrays the load reads from, until it is done
   if (!sp.used || want > sp.cap) {
@@ -1508,7 +1514,7 @@ pic_status sim_load(Sim& S, int inst, int32_t species, double rqm, int64_t n, co
   double wm = 0.0;
   for (double v : hw) wm = std::max(wm, std::fabs(v));
   GridDesc g;
-  if ((st = tiles_for(S, I, n, g)) != PIC_OK || (st = take_tiles(S, I, g)) != PIC_OK) return st;
+  if ((st = tiles_for(S, I, n, g)) != PIC_OK || (st = take_tiles(S, I, g, n)) != PIC_OK) return st;
   const int64_t want = wanted_capacity(I, species, total);
   if (!sp.used || want > sp.cap) {
     int64_t cap = I.cfg.capacity > 0 ? std::max<int64_t>(I.cfg.capacity, want) : want;
@@ -1613,7 +1619,7 @@ pic_status settle_tiles(Sim& S) {
     if (I.settled) continue;
     const int64_t n = instance_particles(I);
     if (n == 0) continue;
-    if (tile_open(I)) {
+    if (tile_open(I) && I.tiled_for != n) {
       GridDesc g;
       pic_status st = setup_grid(S, I.cfg, S.sort_interval, g, (double)n / I.g.ncell);
       if (st == PIC_OK && !same_tiles(g, I.g)) st = retile(S, I, g);
