@@ -84,14 +84,16 @@ __device__ __forceinline__ void block_scan2(int a, int b, int& ea, int& eb, int&
 }
 
 // Offsets and work items of tile t, whose c particles start at ra and whose
-// items start at rb, into buffer set nxt.
+// items start at rb, into buffer set nxt.  (A moving window whose plasma outgrows
+// the store is reported by plan_commit; until the host sees that, the items end
+// with the arrays, as what the scatter writes does.)
 __device__ __forceinline__ void plan_tile(const StoreDesc& S, int nxt, int t, int c, int ra, int rb) {
   S.toff[nxt][t] = ra;
   S.ioff[nxt][t] = rb;
   const int size = pic_item_size(c, S.chunk);
   int4* items = (int4*)S.items[nxt];
   for (int b = 0, k = rb; b < c && k < S.max_items; b += size, k++)
-    items[k] = make_int4(t, ra + b, ra + min(b + size, c), 0);
+    items[k] = make_int4(t, min(ra + b, S.cap), min(ra + min(b + size, c), S.cap), 0);
 }
 
 // End of a check: totals of the planned set (act) and the control words.  One
