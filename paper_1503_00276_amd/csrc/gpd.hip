@@ -1651,6 +1651,14 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
     coherent = btop * (float)(column * ext[2]) > 64.0f * bmax * (float)(it.end - it.begin);
   }
 
+  // (the int64 mode: the instance's own fixed point, as in the one-phase kernel)
+  auto exponent = [&](float top) {
+    int eg = 0;
+    (void)frexpf(g.jscale, &eg);  // jscale = 2^(eg-1)
+    return __builtin_amdgcn_readfirstlane(kWide ? eg - 1 : item_exponent32(top));
+  };
+  int e_item = exponent(btop);
+
   // 3. store the new state at the item's interleaved slots (the LDS of the
   // staged fields is free), then clear the current tile over it
   {
@@ -1671,11 +1679,7 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
       idp[q] = pid[r];
     }
   }
-  if (coherent) btop = fminf(btop, bmax * sred[4 * (kBlock / 64)]);
-  // (the int64 mode: the instance's own fixed point, as in the one-phase kernel)
-  int eg = 0;
-  (void)frexpf(g.jscale, &eg);  // jscale = 2^(eg-1)
-  const int e_item = __builtin_amdgcn_readfirstlane(kWide ? eg - 1 : item_exponent32(btop));
+  if (coherent) e_item = exponent(fminf(btop, bmax * sred[4 * (kBlock / 64)]));
   const float Q = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, e_item))));
   for (int idx = tid; idx < 3 * jpl; idx += nthr) sJ[idx] = (Acc)0;
   if (tid == 0) {
