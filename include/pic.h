@@ -68,7 +68,10 @@ typedef enum {
  * contributions of a tile are summed exactly in integers in LDS.  The unit
  * follows the plasma: in the two-phase kernels (periodic 3D; periodic 2D with
  * items of at most 1024 particles), whose tile sums are 32-bit, the sum of
- * |w| |v_d| over the work item (unit 2^-30 of it at most); in the other
+ * |w| |v_d| over the work item (unit 2^-30 of it at most; in a plasma that moves
+ * as one this grows with the particles of an item, except that tiles of whole
+ * power-of-two columns in 3D count the particles that can reach a node
+ * instead); in the other
  * kernels, whose tile sums are int64, a per-step bound of the species on a
  * single contribution |w| |v|
  * (unit 2^-31 of the bound); the instance's 2^-31 max|w| with
@@ -80,7 +83,11 @@ enum {
                               sum is the compensated accumulation */
   PIC_ACC_FIXED64 = 2      /* tiles folded in int64 too: the current is
                               independent of the order of the adds (bitwise
-                              reproducible), converted to FP32 once per step */
+                              reproducible), converted to FP32 once per step.
+                              Fields, particles (by load order), energies and
+                              momentum of such a run then repeat bit for bit
+                              too; RHO and the residuals, which add in FP64 in
+                              any order, to their rounding */
 };
 
 /* Simulation configuration (the deck's grid, space, time and EM-field

@@ -2,8 +2,8 @@
 // particle positions, Gauss-law residual div E - rho (Hemker 2000, Ch. 3,
 // Sec. 3.1, Eq. maxwell-1 in normalised units), charge-conservation residual
 // (rho1 - rho0)/dt + div J (Sec. 3.2, Eq. continuity), and compensated
-// (Neumaier) FP64 sums of the field and particle energies and momentum; plus
-// the state export.
+// (Neumaier) FP64 sums of the field and particle energies and momentum (exact
+// ones of the particles with the int64 current); plus the state export.
 #include "pic_dev.h"
 #include "pic_kernels.h"
 

@@ -44,7 +44,10 @@ template <> struct YeeTile<3> { static constexpr int X = 16, Y = 4, Z = 4; };
 // runtime extent), and the current is loaded with the staging instead of after
 // two barriers.  Per step, with rows and late loads and so: 64x64 6.4 -> 4.6 us,
 // 300x200 7.0 -> 5.7, 1024x256 9.8 -> 9.1, 45x37x53 12.2 -> 8.6, 128x64x64
-// 28.1 -> 25.2, r-z 384x96 10.3 -> 7.7.
+// 28.1 -> 25.2 (25.9 in the committed trace; these are boxes full of particles,
+// whose kernel leaves nothing of the fields in the caches), r-z 384x96 10.3 ->
+// 7.7.
+
 // Periodic wrap for an index at most one period out of range.
 __device__ __forceinline__ int wrap1(int v, int n) {
   v = v < 0 ? v + n : v;
@@ -52,17 +55,15 @@ __device__ __forceinline__ int wrap1(int v, int n) {
   return v >= n ? v - n : v;
 }
 
-// WIN: compiled with the moving-window terms (launched for groups that hold a
-// moving window).
 // Which field step a periodic 3D box takes: runs of planes along z
 // (yee_march3) or 16x4x4 tiles (yee_step).
 // A long run re-reads little (two planes of E and one of B at its start), but
 // its planes are a serial chain of three barriers and one memory latency
 // each, so the run shortens until the box makes 1,024 workgroups (four per
 // CU), down to 8 planes; a box that does not make 512 workgroups of 8-plane
-// runs takes yee_step's 16x4x4 tiles, which have no chain.  Measured with
-// tiles and with runs of 8, 16 and 32 planes: 128x64x64 22, 29, 42, 69 us;
-// 160x96x96 46, 47, 52, 70 us; 256x128x128 205, 124, 119, 127 us;
+// runs takes yee_step's 16x4x4 tiles, which have no chain.  Measured in empty
+// boxes, with tiles and with runs of 8, 16 and 32 planes: 128x64x64 22, 29, 42,
+// 69 us; 160x96x96 46, 47, 52, 70 us; 256x128x128 205, 124, 119, 127 us;
 // 512x256x256 1483, 819, 753, 728 us.
 struct MarchTile { static constexpr int X = 32, Y = 8; };
 constexpr int kMarchMin = 8, kMarchMax = 32;
@@ -104,6 +105,8 @@ __device__ __forceinline__ void window_advance(const InstDesc& I, int par) {
   I.win[1 - par] = w;
 }
 
+// WIN: compiled with the moving-window terms (launched for groups that hold a
+// moving window).
 template <int DIM, bool WIN>
 __global__ void __launch_bounds__(kBlock) yee_step(const InstDesc* __restrict__ inst, int par,
                                                    const StoreDesc* __restrict__ plan, int nplan, int npx) {
@@ -829,10 +832,6 @@ __global__ void __launch_bounds__(kBlock) yee_step_rz(const InstDesc* __restrict
     }
 }
 
-// One smoothing pass of the current along 'axis' (pass 'lev' of that axis)
-// for every instance that has it: J <- a J[i-1] + b J[i] + c J[i+1] with the
-// normalised weights, periodic.  The instance's first pass reads the
-// accumulator of the step's parity; later passes read the other buffer.
 // One smoothing pass of an r-z instance.  The filtered quantity is the
 // current density (the deposit divided by the ring volume of its row: radius
 // (j - 1/2) dr for the whole rows of J_z, J_theta, j dr for the half rows of
@@ -1011,6 +1010,11 @@ __global__ void __launch_bounds__(kBlock) smooth_tiles(const InstDesc* __restric
   }
 }
 
+// One smoothing pass of the current along 'axis' (pass 'lev' of that axis)
+// for every instance that has it and is not smoothed in tiles: J <- a J[i-1] +
+// b J[i] + c J[i+1] with the normalised weights, periodic.  The instance's first
+// pass reads the accumulator of the step's parity; later passes read the other
+// buffer.
 __global__ void __launch_bounds__(kBlock) smooth_pass(const InstDesc* __restrict__ inst, int axis, int lev,
                                                       int par) {
   const InstDesc& I = inst[blockIdx.y];

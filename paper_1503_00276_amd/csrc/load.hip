@@ -11,8 +11,9 @@
 //   plan    (one workgroup) tile offsets, work items
 //   slots   (per tile)      place of every (cell, rank) of the tile
 //   place   (per particle)  converted and written to its place
-// Bound by memory: 56 or 64 B of FP64 input read twice and 32 B written twice
-// per particle.  On one host thread (copies to the host included) a load took
+// Bound by memory: 48 or 56 B of FP64 input (2D, 3D) read twice and 32 or 36 B
+// of state written once per particle, besides its rank and its place (4 B each,
+// written and read).  On one host thread (copies to the host included) a load took
 // 2.0 ms for 65,536 particles and about 70 ns for each of 16.8 M.
 #include <climits>
 
