@@ -69,9 +69,9 @@ typedef enum {
  * follows the plasma: in the two-phase kernels (periodic 3D; periodic 2D with
  * items of at most 1024 particles), whose tile sums are 32-bit, the sum of
  * |w| |v_d| over the work item (unit 2^-30 of it at most; in a plasma that moves
- * as one this grows with the particles of an item, except that tiles of whole
- * power-of-two columns in 3D count the particles that can reach a node
- * instead); in the other
+ * as one this grows with the particles of an item, except that the linear and
+ * quadratic 3D kernels count the particles that can reach a node instead in
+ * tiles of more than 64 cells); in the other
  * kernels, whose tile sums are int64, a per-step bound of the species on a
  * single contribution |w| |v|
  * (unit 2^-31 of the bound); the instance's 2^-31 max|w| with

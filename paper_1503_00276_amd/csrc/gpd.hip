@@ -1215,7 +1215,10 @@ __device__ void process_item(const StoreDesc& S, int cur, int unit, const Item i
 // 64 cells).  There a second bound counts the particles that can reach a node
 // (class_reach): 3.2e-8, and the default tiles stay no coarser than 64 cells
 // were.  96^3 cells, thermal, us a step without and with it: linear at 1 and 4
-// per cell 118 and 122, 192 and 199; quadratic 163 and 168, 297 and 303.
+// per cell 118 and 122, 192 and 199; quadratic 163 and 168, 297 and 303.  Tiles
+// whose columns are not the store's classes count them in LDS (column_reach):
+// 108x100x92 cells in 12x8x4 tiles, 2 per cell, thermal and drifting, without and
+// with it: linear 166 and 182, 174 and 192; quadratic 260 and 284, 262 and 295.
 
 constexpr int kSplitR = 3;  // particles per thread per work item
 
@@ -1331,6 +1334,65 @@ __device__ __forceinline__ float class_reach(int n, int ex, int ey) {
   float top = fmaxf(window(window(c, ex, 1, false), ey, ex, true), window(window(c, ex, 1, true), ey, ex, false));
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+  return top * peak;
+}
+
+// The same of tiles whose columns are not the classes (extents that are no powers
+// of two, more than 64 columns), or that are longest along x3: counts over the
+// columns along the tile's shortest axis, in LDS.  key: the particles' cells,
+// x fastest (-1: none); n: free LDS for the counts of all columns; part: a float
+// per wavefront.  Every thread of the workgroup calls it.  Only a plasma that
+// moves as one comes here.
+template <int ORDER>
+__device__ __forceinline__ float column_reach(const int (&key)[kSplitR], const int (&ext)[3], int* n, float* part) {
+  constexpr int H = ORDER == 1 ? 2 : 3;
+  constexpr float peak = shape_peak<ORDER>();
+  constexpr float s1 = ORDER == 1 ? 0.0f : 0.125f;
+  const int tid = threadIdx.x;
+  const int along = ext[2] <= min(ext[0], ext[1]) ? 2 : (ext[1] <= ext[0] ? 1 : 0);
+  const int ea = along == 0 ? ext[1] : ext[0], eb = along == 2 ? ext[1] : ext[2];
+  const int cells = ext[0] * ext[1] * ext[2];
+  for (int i = tid; i < ea * eb; i += kBlock) n[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kSplitR; r++) {
+    if (key[r] < 0) continue;
+    const int c = min(key[r], cells - 1);
+    const int yz = c / ext[0], x = c - yz * ext[0];
+    const int z = yz / ext[1], y = yz - z * ext[1];
+    atomicAdd(&n[(along == 0 ? y : x) + ea * (along == 2 ? y : z)], 1);
+  }
+  __syncthreads();
+  auto tau = [&](int k) {
+    const int far = k < 0 ? -k - 1 : k;
+    return far == 0 ? peak : (far == 1 ? 0.5f * (s1 + peak) : 0.5f * s1);
+  };
+  float top = 0.0f;
+  for (int i = tid; i < ea * eb; i += kBlock) {
+    // cells from H below the node's on, around the tile
+    const int b0 = i / ea, a0 = i - b0 * ea;
+    float sa = 0.0f, sb = 0.0f;  // of the components along the first and the second axis
+    int b = (b0 + H * eb - H) % eb;
+#pragma unroll
+    for (int kb = -H; kb < H; kb++) {
+      int a = (a0 + H * ea - H) % ea;
+#pragma unroll
+      for (int ka = -H; ka < H; ka++) {
+        const float v = (float)n[a + ea * b];
+        if (ka + H < ea) sa += tau(kb) * v;
+        if (kb + H < eb) sb += tau(ka) * v;
+        a = a + 1 < ea ? a + 1 : 0;
+      }
+      b = b + 1 < eb ? b + 1 : 0;
+    }
+    top = fmaxf(top, fmaxf(sa, sb));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+  if ((tid & 63) == 0) part[tid >> 6] = top;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; w++) top = fmaxf(top, part[w]);
   return top * peak;
 }
 
@@ -1583,7 +1645,8 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
         sen[r][d] = en[d];
       }
       sncell[r] = pic_pack(g, nc[0], nc[1], nc[2]);
-      skey[r] = (lk[0] + ext[0] * (lk[1] + ext[1] * lk[2])) & 63;
+      skey[r] = lk[0] + ext[0] * (lk[1] + ext[1] * lk[2]);
+      skey[r] = kColumns ? max(skey[r], 0) : skey[r] & 63;
       snu[r][0] = ux;
       snu[r][1] = uy;
       snu[r][2] = uz;
@@ -1620,8 +1683,9 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
   // (The default tiles of the cubic shape and the 4x4xN ones need none.)
   constexpr float peak2 = shape_peak<ORDER>() * shape_peak<ORDER>();
   const int column = ext[0] * ext[1];
-  const bool columns = kColumns && column <= 64 && (column & (column - 1)) == 0 && (float)(column * ext[2]) * peak2 > 64.0f;
-  if (columns) {
+  const bool large = kColumns && (float)(column * ext[2]) * peak2 > 64.0f;
+  const bool classes = column <= 64 && (column & (column - 1)) == 0 && ext[2] <= max(4, min(ext[0], ext[1]));
+  if (large) {
     float bm = 0.0f;
 #pragma unroll
     for (int r = 0; r < R; r++)
@@ -1642,10 +1706,10 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
   btop *= peak2;
   // A plasma that moves as one sums to more than the particles of 64 cells at
   // the largest |w| |move| would: then the second bound is that largest times
-  // the particles that can reach a node (class_reach).
+  // the particles that can reach a node (class_reach, column_reach).
   float bmax = 0.0f;
   bool coherent = false;
-  if (columns) {
+  if (large) {
 #pragma unroll
     for (int w = 0; w < kBlock / 64; w++) bmax = fmaxf(bmax, sred[3 * (kBlock / 64) + w]);
     coherent = btop * (float)(column * ext[2]) > 64.0f * bmax * (float)(it.end - it.begin);
@@ -1662,8 +1726,10 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
   // 3. store the new state at the item's interleaved slots (the LDS of the
   // staged fields is free), then clear the current tile over it
   {
-    int pos[R];
-    interleave_slots<ORDER>(skey, pos, smem, coherent ? ext[0] : 0, ext[1], &sred[4 * (kBlock / 64)]);
+    int pos[R], cls[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) cls[r] = kColumns && skey[r] >= 0 ? skey[r] & 63 : skey[r];
+    interleave_slots<ORDER>(cls, pos, smem, coherent && classes ? ext[0] : 0, ext[1], &sred[4 * (kBlock / 64)]);
 #pragma unroll
     for (int r = 0; r < R; r++) {
       if (pos[r] < 0) continue;
@@ -1679,7 +1745,11 @@ __device__ void process_item3(const StoreDesc& S, int cur, const Item it, int ii
       idp[q] = pid[r];
     }
   }
-  if (coherent) e_item = exponent(fminf(btop, bmax * sred[4 * (kBlock / 64)]));
+  if (coherent) {
+    const float reach =
+        classes ? sred[4 * (kBlock / 64)] : column_reach<ORDER>(skey, ext, (int*)smem, &sred[3 * (kBlock / 64)]);
+    e_item = exponent(fminf(btop, bmax * reach));
+  }
   const float Q = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ldexpf(1.0f, e_item))));
   for (int idx = tid; idx < 3 * jpl; idx += nthr) sJ[idx] = (Acc)0;
   if (tid == 0) {

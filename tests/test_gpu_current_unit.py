@@ -88,3 +88,30 @@ def test_an_infinite_momentum_does_not_take_its_neighbours_current(nx, order):
         got.append(sim.current())
         sim.close()
     assert rel_max(got[1], got[0]) <= J_TOL
+
+
+# As above in tiles whose columns are not 64 classes, or that are longest along
+# x3: a node's reach is 48 particles of a uniform plasma (45), times the shortest
+# extent over four.
+@pytest.mark.parametrize("order,factor", [(1, 1.3), (2, 2.0)])
+@pytest.mark.parametrize("tile", [(12, 8, 4), (6, 8, 4), (9, 8, 4), (4, 8, 8), (4, 8, 12), (8, 4, 12), (24, 8, 4)],
+                         ids=lambda t: "x".join(map(str, t)))
+def test_a_drifting_plasma_keeps_its_unit_in_any_large_tile(orc, order, factor, tile):
+    nx, ppc = (48, 24, 24), 1
+    rng = np.random.default_rng(ppc)
+    c = np.indices(nx).reshape(3, -1).T
+    x = (c + rng.random(c.shape)) * 0.2
+    u, w = np.tile((10.0, 4.0, 2.0), (len(x), 1)), np.full(len(x), -1.0 / ppc)
+    print("drift", order, tile, flush=True)
+    rms, top, _ = _current_error(orc, nx, order, x, u, w, tile=tile)
+    small, _, _ = _current_error(orc, nx, order, x, u, w, tile=(4, 4, 4))
+    print("rms %.3e, in 4x4x4 tiles %.3e" % (rms, small), flush=True)
+    assert top <= J_TOL
+    assert rms <= factor * small
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("tile", [(12, 6, 4), (4, 6, 12), (6, 8, 8), (12, 4, 6), (6, 6, 6)],
+                         ids=lambda t: "x".join(map(str, t)))
+def test_a_dense_spot_does_not_overflow_its_node_in_any_tile(orc, order, tile):
+    test_a_dense_spot_does_not_overflow_its_node(orc, order, tile)
