@@ -115,3 +115,22 @@ def test_a_drifting_plasma_keeps_its_unit_in_any_large_tile(orc, order, factor, 
                          ids=lambda t: "x".join(map(str, t)))
 def test_a_dense_spot_does_not_overflow_its_node_in_any_tile(orc, order, tile):
     test_a_dense_spot_does_not_overflow_its_node(orc, order, tile)
+
+
+# The cubic shape and the 4x4xN tiles, which take the sum alone, and odd boxes: the
+# sum of a uniform plasma over a default tile is that of 64 cells at most where
+# the axes have such tiles.
+@pytest.mark.parametrize("nx,order", [((36, 42, 36), 3), ((12, 21, 36), 3), ((16, 12, 48), 3), ((4, 4, 48), 1),
+                                      ((4, 4, 48), 2), ((16, 4, 48), 2)])
+def test_default_tiles_that_take_the_sum_are_small(nx, order):
+    from paper_1503_00276_amd import pic
+
+    sim = pic.Pic(pic.Config(ndim=3, nx=nx, dx=(0.2,) * 3, dt=0.1, shape_order=order))
+    rng = np.random.default_rng(1)
+    n = int(np.prod(nx))
+    sim.load_particles(rng.random((n, 3)) * np.asarray(nx) * 0.2, rng.normal(0, 0.1, (n, 3)), np.full(n, -1.0))
+    t = sim.info().tile
+    sim.close()
+    peak = (1.0, 0.75, 2.0 / 3.0)[order - 1]
+    sums = (order == 3) or (t[0] == 4 and t[1] == 4)
+    assert not sums or t[0] * t[1] * t[2] * peak**2 <= 64.0, list(t)
